@@ -497,6 +497,9 @@ jq_status jq_gemm_plan(int64_t M, int64_t N, int64_t K, int cus, int* tile_rows)
  * an M x K by K x N product on a device with `cus` compute units, for checking
  * and tuning: *waves = 8 (one 8-wave block per CU) or 4 (two 4-wave blocks per
  * CU), *tile_rows = the rows of activations per output tile (256 columns).
+ * Products with too few such tiles to fill the device (few tokens, narrow
+ * weights) take a kernel of smaller tiles instead; the plan is then the one
+ * they would have had.
  * Host-only; launches nothing.
  * Errors: JQ_ERR_INVALID_ARG, JQ_ERR_UNSUPPORTED_SHAPE.
  */

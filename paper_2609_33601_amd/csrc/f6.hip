@@ -44,7 +44,8 @@
 //     lane (the vector memory path costs about the same per instruction
 //     whatever its width).
 //
-// GEMM structure.  Persistent blocks walk the output tiles (256 n columns
+// GEMM structure.  (Products with few output tiles go to f6_narrow.hip.)
+// Persistent blocks walk the output tiles (256 n columns
 // each) in an XCD-aware order, in one of two shapes:
 //   * one 8-wave block per CU (two waves per SIMD) on tiles of
 //     32 * tile_bands rows, tile_bands 7 or 8 picked per shape to spread the
@@ -116,6 +117,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "f6_common.h"
 #include "gemm_common.h"
 #include "jq.h"
 #include "jq_internal.h"
@@ -125,15 +127,13 @@ namespace jq {
 namespace {
 
 using namespace gemm_detail;
+using namespace f6_detail;
 
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 typedef unsigned v6u __attribute__((ext_vector_type(6)));
 typedef float v16f32 __attribute__((ext_vector_type(16)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned v4u32 __attribute__((ext_vector_type(4)));
 
-constexpr int kFragBytes = 1536;          // one 32-row x 64-code fragment
 constexpr int kFBN = 256;                 // block tile columns
 constexpr int kDmaPerWave = 3;            // stage DMA instructions per wave
 constexpr int64_t kShortK = 6144;          // largest K that may take the two-block shape
@@ -591,9 +591,7 @@ __global__ __launch_bounds__(256) void int4_to_f6_kernel(const uint8_t* __restri
 // ---------------------------------------------------------------------------
 // GEMM
 
-typedef int v4i32 __attribute__((ext_vector_type(4)));
 typedef unsigned v2u32 __attribute__((ext_vector_type(2)));
-typedef int v2i32 __attribute__((ext_vector_type(2)));
 
 struct WFrag {
   v8i f[2][2];  // [k-step][band]; dwords 0..5 used
@@ -654,7 +652,6 @@ constexpr int kWaitcntBase = (0x7 << 4) | (0xF << 8);  // expcnt, lgkmcnt: no wa
 constexpr int vmcnt_imm(int n) { return kWaitcntBase | (n & 0xF) | ((n >> 4) << 14); }
 constexpr int kLgkm0 = 0xC07F;                          // lgkmcnt(0), vmcnt and expcnt: no wait
 constexpr int kWLoads = 6;                              // weight loads per wave per stage
-constexpr uint32_t kOutside = 0x80000000u;              // a buffer offset past every operand
 
 // BIAS_TAIL: a bias with odd N, whose last value the epilogue of a ragged
 // tile reads from memory (its staged pair reads past the buffer as zero);
@@ -1585,6 +1582,8 @@ hipError_t launch_w4a4_f6_gemm(Epilogue epi, const uint8_t* xf6, const float* sx
   if (e != hipSuccess) return e;
   const int ksteps = static_cast<int>(f6_ksteps(K));
   const int64_t slots = std::max<int64_t>(kNumXcd, cus / kNumXcd * kNumXcd);
+  if (const int tile = f6_narrow_tile(M, N, K, slots))
+    return launch_f6_narrow(tile, epi, xf6, sx, M, K, wf6, sw, N, bias, out, st);
   const int waves = f6_block_waves(M, N, K, slots);
   const int tile_bands = waves == 4 ? 4 : f6_tile_bands(M, N, slots);
   const int tiles_m = static_cast<int>((M + 32 * tile_bands - 1) / (32 * tile_bands));

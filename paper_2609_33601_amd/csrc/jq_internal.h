@@ -58,6 +58,14 @@ int f6_block_waves(int64_t M, int64_t N, int64_t K, int64_t slots);
 // GEMM tile height in bands of 32 rows (7 or 8) for an M x N output on `slots` CUs.
 int f6_tile_bands(int64_t M, int64_t N, int64_t slots);
 
+// The GEMM's kernel for products with few output tiles: which of its tiles an
+// M x K by K x N product on `cus` CUs takes (0: none, it goes to the tiled
+// kernel), and its launch.
+int f6_narrow_tile(int64_t M, int64_t N, int64_t K, int64_t cus);
+hipError_t launch_f6_narrow(int tile, Epilogue epi, const uint8_t* xf6, const float* sx, int64_t M, int64_t K,
+                            const uint8_t* wf6, const float* sw, int64_t N, const uint16_t* bias, void* out,
+                            hipStream_t st);
+
 // Per-token quantiser writing the BF6 activation operand and the scales.
 hipError_t launch_quantize_rows_f6(const uint16_t* x, int64_t M, int64_t K, uint8_t* out, float* scale,
                                    hipStream_t st);
