@@ -1100,7 +1100,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Group-wise GEMM on BF6 operands
+// Group-wise GEMM on BF6 operands (products with few output tiles go to
+// f6_narrow_group.hip)
 //
 // S[m,n] = sum over the groups g in k order of fl32(fl32(acc_g * s_x[m,g]) *
 // s_w[n,g]), acc_g the exact integer product over the G codes of group g (a
@@ -1529,6 +1530,13 @@ hipError_t launch_quantize_groups_f6(const uint16_t* x, int64_t M, int64_t K, in
 hipError_t launch_w4a4g_f6_gemm(Epilogue epi, const uint8_t* xf6, const float* sx, int64_t M, int64_t K, int G,
                                 const uint8_t* wf6, const float* sw, int64_t N, const uint16_t* bias, void* out,
                                 hipStream_t st) {
+  int dev = 0, cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  if (const int waves = f6_narrow_group_waves(M, N, K, G, std::max<int64_t>(kNumXcd, cus / kNumXcd * kNumXcd)))
+    return launch_f6_narrow_group(waves, epi, xf6, sx, M, K, G, wf6, sw, N, bias, out, st);
   const int ksteps = static_cast<int>(f6_ksteps(K));
   const int tiles_m = static_cast<int>((M + 127) / 128), tiles_n = static_cast<int>((N + 127) / 128);
   const int64_t tiles = static_cast<int64_t>(tiles_m) * tiles_n;

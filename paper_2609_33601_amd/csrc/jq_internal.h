@@ -66,6 +66,13 @@ hipError_t launch_f6_narrow(int tile, Epilogue epi, const uint8_t* xf6, const fl
                             const uint8_t* wf6, const float* sw, int64_t N, const uint16_t* bias, void* out,
                             hipStream_t st);
 
+// The same for the group-wise GEMM: waves per block of its narrow kernel (0:
+// the tiled kernel), and the launch.
+int f6_narrow_group_waves(int64_t M, int64_t N, int64_t K, int G, int64_t cus);
+hipError_t launch_f6_narrow_group(int waves, Epilogue epi, const uint8_t* xf6, const float* sx, int64_t M, int64_t K,
+                                  int G, const uint8_t* wf6, const float* sw, int64_t N, const uint16_t* bias,
+                                  void* out, hipStream_t st);
+
 // Per-token quantiser writing the BF6 activation operand and the scales.
 hipError_t launch_quantize_rows_f6(const uint16_t* x, int64_t M, int64_t K, uint8_t* out, float* scale,
                                    hipStream_t st);
