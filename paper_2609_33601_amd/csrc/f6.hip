@@ -14,7 +14,8 @@
 // operands reach it already encoded, so the loop holds no widening
 // arithmetic at all:
 //   * activations are quantised straight into BF6 by quantize_rows4_f6_kernel
-//     (four rows per block) or quantize_rows_f6_kernel (longer rows), with
+//     (four rows per block) or quantize_rows_f6_kernel (longer rows), or the
+//     kernel of f6_quant_few.hip (few rows), with
 //     the same scale and codes as the packed-int4 quantiser;
 //   * weights are converted once, offline, from the canonical packed int4
 //     (or ternary) codes.
@@ -129,15 +130,12 @@ namespace {
 using namespace gemm_detail;
 using namespace f6_detail;
 
-typedef unsigned v6u __attribute__((ext_vector_type(6)));
 typedef float v16f32 __attribute__((ext_vector_type(16)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned v4u32 __attribute__((ext_vector_type(4)));
 
 constexpr int kFBN = 256;                 // block tile columns
 constexpr int kDmaPerWave = 3;            // stage DMA instructions per wave
 constexpr int64_t kShortK = 6144;          // largest K that may take the two-block shape
-constexpr int kQuantBatchMax = 8;          // inputs of one batched quantiser launch
 
 // The GEMM comes in two block shapes (WAVES = 8 or 4 waves of 64): one
 // 8-wave block per CU on a tile of up to 256 activation rows, or two 4-wave
@@ -164,12 +162,6 @@ __device__ __forceinline__ v6u bf6_group(const float* q) {
   }
   return __builtin_amdgcn_cvt_scalef32_2xpk16_bf6_f32(ev, od, 1.0f);
 }
-
-constexpr float kMagic = 12582912.0f;         // 1.5 * 2^23
-constexpr float kNearTie = 0.5f - 0x1p-17f;
-
-__device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
-__device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 
 // Codes of one 32-element group (16 dwords of bf16 pairs).  Reciprocal path
 // with the exact IEEE division wherever the product sits next to a rounding
@@ -1450,6 +1442,7 @@ int f6_block_waves(int64_t M, int64_t N, int64_t K, int64_t slots) {
 
 template <int G>
 hipError_t launch_quantize_f6(const uint16_t* x, int64_t M, int64_t K, uint8_t* out, float* scale, hipStream_t st) {
+  if (f6_quantize_few_rows(M)) return launch_quantize_few_f6(x, M, K, G, out, scale, st);
   const int64_t ksteps = f6_ksteps(K);
   const int64_t groups = 2 * ksteps;
   if (groups <= 512) {
@@ -1477,10 +1470,15 @@ hipError_t launch_quantize_rows_f6(const uint16_t* x, int64_t M, int64_t K, uint
 
 hipError_t launch_quantize_rows_f6_batch(int count, const uint16_t* const* x, const int64_t* M, const int64_t* K,
                                          uint8_t* const* out, float* const* scale, hipStream_t st) {
-  // Inputs whose rows fit the four-rows-per-block kernel (at most 512 groups)
-  // share one launch: its waves are the most any of them needs, and NJ the
+  // Inputs of few rows all share a launch of the few-row kernel.  Otherwise
+  // inputs whose rows fit the four-rows-per-block kernel (at most 512 groups)
+  // share one of that, few rows or many (a short input costs less inside
+  // the pass over a long one than as a launch of its own): its waves are the most any of them needs, and NJ the
   // most sets of groups any of them needs at that wave count.  Longer rows get
   // a launch of their own, on the same stream.
+  bool few = true;
+  for (int i = 0; i < count; ++i) few = few && f6_quantize_few_rows(M[i]);
+  if (few) return launch_quantize_few_f6_batch(count, x, M, K, out, scale, st);
   Q4Batch b{};
   int waves = 1;
   for (int i = 0; i < count; ++i) {

@@ -82,6 +82,15 @@ hipError_t launch_quantize_rows_f6(const uint16_t* x, int64_t M, int64_t K, uint
 hipError_t launch_quantize_rows_f6_batch(int count, const uint16_t* const* x, const int64_t* M, const int64_t* K,
                                          uint8_t* const* out, float* const* scale, hipStream_t st);
 
+// The BF6 quantisers' kernel for few rows (G = 0: per token): whether an input
+// of M rows goes there, its launch, and its batched form (every input of few
+// rows, count <= 8).
+bool f6_quantize_few_rows(int64_t M);
+hipError_t launch_quantize_few_f6(const uint16_t* x, int64_t M, int64_t K, int G, uint8_t* out, float* scale,
+                                  hipStream_t st);
+hipError_t launch_quantize_few_f6_batch(int count, const uint16_t* const* x, const int64_t* M, const int64_t* K,
+                                        uint8_t* const* out, float* const* scale, hipStream_t st);
+
 // Group-wise BF6 engine (G = 64 or 128): the group quantiser writing the BF6
 // activation operand and scales [M, K/G]; the group GEMM on BF6 operands with
 // scales [M, K/G] and [N, K/G] (epi kBf16 or kF32).
