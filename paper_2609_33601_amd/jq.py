@@ -99,31 +99,46 @@ def _check(status, where):
         raise JQError(status, where)
 
 
-def _torch():
-    import torch
+_torch_module = None
 
-    return torch
+
+def _torch():
+    global _torch_module
+    if _torch_module is None:
+        import torch
+
+        _torch_module = torch
+    return _torch_module
+
+
+# The marshalling of one call is on the path of every few-token layer: with
+# two kernels of 4.5 us each, a layer's pass used to be bound by 15 us of
+# Python.  Pointers are passed as plain integers, the current stream is read
+# without building a Stream object, and a tensor that is as it should be takes
+# one test (see _dev).
 
 
 def _stream_ptr(stream):
-    torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    c = _torch()._C
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
 
 def _dev(t, dtype, shape, name):
+    """The device pointer of `t`, which must be a contiguous GPU tensor of this dtype (and shape)."""
     torch = _torch()
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
+    if t.is_cuda and t.dtype is dtype and (shape is None or t.shape == shape) and t.is_contiguous():
+        return t.data_ptr()
     if t.device.type != "cuda":
         raise ValueError(f"{name} must be on the GPU, got {t.device}")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    raise ValueError(f"{name} must be contiguous")
 
 
 def jq_w4a4_workspace_bytes(M, K):
@@ -170,7 +185,7 @@ def jq_w4a4_linear(x, wq, w_scale, bias=None, y=None, workspace=None, stream=Non
     need = jq_w4a4_workspace_bytes(M, K)
     if workspace is None:
         workspace = torch.empty((need,), dtype=torch.uint8, device=x.device)
-    bptr = ctypes.c_void_p(None) if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
+    bptr = None if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
     st = lib().jq_w4a4_linear(_dev(x, torch.bfloat16, None, "x"), M, K,
                               _dev(wq, torch.uint8, (N, K // 2), "wq"),
                               _dev(w_scale, torch.float32, (N,), "w_scale"), N, bptr,
@@ -189,7 +204,7 @@ def jq_w4a4_gemm(q, scale, wq, w_scale, bias=None, y=None, stream=None):
     N = wq.shape[0]
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=q.device)
-    bptr = ctypes.c_void_p(None) if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
+    bptr = None if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
     st = lib().jq_w4a4_gemm(_dev(q, torch.uint8, (M, Kh), "q"), _dev(scale, torch.float32, (M,), "scale"),
                             M, K, _dev(wq, torch.uint8, (N, Kh), "wq"),
                             _dev(w_scale, torch.float32, (N,), "w_scale"), N, bptr,
@@ -242,7 +257,7 @@ def jq_w158a4_linear(x, wt, w_scale, bias=None, y=None, workspace=None, stream=N
     need = jq_w4a4_workspace_bytes(M, K)
     if workspace is None:
         workspace = torch.empty((need,), dtype=torch.uint8, device=x.device)
-    bptr = ctypes.c_void_p(None) if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
+    bptr = None if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
     st = lib().jq_w158a4_linear(_dev(x, torch.bfloat16, None, "x"), M, K,
                                 _dev(wt, torch.uint8, (N, K // 4), "wt"),
                                 _dev(w_scale, torch.float32, (N,), "w_scale"), N, bptr,
@@ -261,7 +276,7 @@ def jq_w158a4_gemm(q, scale, wt, w_scale, bias=None, y=None, stream=None):
     N = wt.shape[0]
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=q.device)
-    bptr = ctypes.c_void_p(None) if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
+    bptr = None if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
     st = lib().jq_w158a4_gemm(_dev(q, torch.uint8, (M, Kh), "q"), _dev(scale, torch.float32, (M,), "scale"),
                               M, K, _dev(wt, torch.uint8, (N, K // 4), "wt"),
                               _dev(w_scale, torch.float32, (N,), "w_scale"), N, bptr,
@@ -326,7 +341,7 @@ def jq_w4a4g_linear(x, wq, w_scale, G, bias=None, y=None, workspace=None, stream
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
     if workspace is None:
         workspace = torch.empty((jq_w4a4g_workspace_bytes(M, K, G),), dtype=torch.uint8, device=x.device)
-    bptr = ctypes.c_void_p(None) if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
+    bptr = None if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
     st = lib().jq_w4a4g_linear(_dev(x, torch.bfloat16, None, "x"), M, K, G,
                                _dev(wq, torch.uint8, (N, K // 2), "wq"),
                                _dev(w_scale, torch.float32, (N, K // G), "w_scale"), N, bptr,
@@ -345,7 +360,7 @@ def jq_w4a4g_gemm(q, scale, wq, w_scale, G, bias=None, y=None, stream=None):
     N = wq.shape[0]
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=q.device)
-    bptr = ctypes.c_void_p(None) if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
+    bptr = None if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
     st = lib().jq_w4a4g_gemm(_dev(q, torch.uint8, (M, Kh), "q"), _dev(scale, torch.float32, (M, K // G), "scale"),
                              M, K, G, _dev(wq, torch.uint8, (N, Kh), "wq"),
                              _dev(w_scale, torch.float32, (N, K // G), "w_scale"), N, bptr,
@@ -455,7 +470,7 @@ def jq_w4a4_f6_linear(x, wf6, w_scale, bias=None, y=None, workspace=None, stream
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
     if workspace is None:
         workspace = torch.empty((jq_w4a4_f6_workspace_bytes(M, K),), dtype=torch.uint8, device=x.device)
-    bptr = ctypes.c_void_p(None) if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
+    bptr = None if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
     st = lib().jq_w4a4_f6_linear(_dev(x, torch.bfloat16, None, "x"), M, K,
                                  _dev(wf6, torch.uint8, (jq_f6_operand_bytes(N, K),), "wf6"),
                                  _dev(w_scale, torch.float32, (N,), "w_scale"), N, bptr,
@@ -480,7 +495,7 @@ def jq_quantize_act_f6_batch(xs, xf6s=None, scales=None, stream=None):
         scales = [torch.empty((x.shape[0],), dtype=torch.float32, device=x.device) for x in xs]
     if not (len(xf6s) == len(scales) == n):
         raise ValueError("xs, xf6s and scales must have the same length")
-    ptrs = lambda vals: (ctypes.c_void_p * max(n, 1))(*[v.value for v in vals])
+    ptrs = lambda vals: (ctypes.c_void_p * max(n, 1))(*vals)
     xp = ptrs([_dev(x, torch.bfloat16, None, f"xs[{i}]") for i, x in enumerate(xs)])
     qp = ptrs([_dev(q, torch.uint8, (jq_f6_operand_bytes(*x.shape),), f"xf6s[{i}]")
                for i, (x, q) in enumerate(zip(xs, xf6s))])
@@ -504,7 +519,7 @@ def jq_w4a4_f6_linear_noalloc(x, wf6, w_scale, bias=None, y=None, stream=None):
     N = w_scale.shape[0]
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
-    bptr = ctypes.c_void_p(None) if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
+    bptr = None if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
     st = lib().jq_w4a4_f6_linear_noalloc(_dev(x, torch.bfloat16, None, "x"), M, K,
                                          _dev(wf6, torch.uint8, (jq_f6_operand_bytes(N, K),), "wf6"),
                                          _dev(w_scale, torch.float32, (N,), "w_scale"), N, bptr,
@@ -519,7 +534,7 @@ def jq_w4a4_f6_gemm(xf6, scale, K, wf6, w_scale, bias=None, y=None, stream=None)
     M, N = scale.shape[0], w_scale.shape[0]
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=xf6.device)
-    bptr = ctypes.c_void_p(None) if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
+    bptr = None if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
     st = lib().jq_w4a4_f6_gemm(_dev(xf6, torch.uint8, (jq_f6_operand_bytes(M, K),), "xf6"),
                                _dev(scale, torch.float32, (M,), "scale"), M, K,
                                _dev(wf6, torch.uint8, (jq_f6_operand_bytes(N, K),), "wf6"),
@@ -598,7 +613,7 @@ def jq_w4a4g_f6_linear(x, wf6, w_scale, G, bias=None, y=None, workspace=None, st
         y = torch.empty((M, N), dtype=torch.bfloat16, device=x.device)
     if workspace is None:
         workspace = torch.empty((jq_w4a4g_f6_workspace_bytes(M, K, G),), dtype=torch.uint8, device=x.device)
-    bptr = ctypes.c_void_p(None) if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
+    bptr = None if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
     st = lib().jq_w4a4g_f6_linear(_dev(x, torch.bfloat16, None, "x"), M, K, G,
                                   _dev(wf6, torch.uint8, (jq_f6_operand_bytes(N, K),), "wf6"),
                                   _dev(w_scale, torch.float32, (N, K // G), "w_scale"), N, bptr,
@@ -617,7 +632,7 @@ def jq_w4a4g_f6_gemm(xf6, scale, wf6, w_scale, G, bias=None, y=None, stream=None
     K = KG * G
     if y is None:
         y = torch.empty((M, N), dtype=torch.bfloat16, device=xf6.device)
-    bptr = ctypes.c_void_p(None) if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
+    bptr = None if bias is None else _dev(bias, torch.bfloat16, (N,), "bias")
     st = lib().jq_w4a4g_f6_gemm(_dev(xf6, torch.uint8, (jq_f6_operand_bytes(M, K),), "xf6"),
                                 _dev(scale, torch.float32, (M, KG), "scale"), M, K, G,
                                 _dev(wf6, torch.uint8, (jq_f6_operand_bytes(N, K),), "wf6"),
