@@ -6,7 +6,7 @@
 //   y[m,n] = bf16_rne(((fp32(acc) * sx[m]) * sw[n]) + bias[n])
 // with every fp32 operation rounded on its own (built with -ffp-contract=off).
 //
-// Structure.
+// Structure.  (Products with few output tiles go to gemm_narrow.hip.)
 //  * Block tile 128 (m) x 256 (n), four waves of 64 x 128 outputs each (a
 //    4 x 8 grid of 16 x 16 MFMA tiles, 128 int32 accumulators per lane).  A
 //    block needs 64 KiB of LDS and at most 256 registers per lane, so two
@@ -100,31 +100,6 @@ struct WTraits {
 // Ternary weight rows are 32 bytes (two chunks); rows 8..15 of every 16 swap
 // their chunks, so the 32 lanes of a ds_read_b64 half cover all 64 banks.
 __device__ __forceinline__ int wt_slot(int row, int c) { return row * 2 + (c ^ ((row >> 3) & 1)); }
-
-// Widen 16 ternary codes (one packed dword, code i in bits 2i .. 2i+1) to
-// int8 64 * code: dword d, byte b of the result holds code 4b + d.  Shifting
-// a 2-bit field to the top of its byte sign-extends it for free.
-__device__ __forceinline__ v4i unpack_tern(uint32_t p) {
-  v4i r;
-  r[0] = static_cast<int>((p << 6) & 0xC0C0C0C0u);
-  r[1] = static_cast<int>((p << 4) & 0xC0C0C0C0u);
-  r[2] = static_cast<int>((p << 2) & 0xC0C0C0C0u);
-  r[3] = static_cast<int>(p & 0xC0C0C0C0u);
-  return r;
-}
-
-// Widen 16 int4 activation codes (p0: codes 0..7, p1: codes 8..15) into the
-// order unpack_tern produces: dword d, byte b = 16 * code 4b + d.
-__device__ __forceinline__ v4i unpack8_tern_order(uint32_t p0, uint32_t p1) {
-  const v4i e = unpack8(p0, p1);  // e[0] = codes 0 2 4 6, e[1] = 1 3 5 7, e[2] = 8 10 12 14, e[3] = 9 11 13 15
-  v4i r;
-  // v_perm_b32: selector byte values 0..3 pick the second operand's bytes, 4..7 the first's.
-  r[0] = static_cast<int>(__builtin_amdgcn_perm(static_cast<uint32_t>(e[2]), static_cast<uint32_t>(e[0]), 0x06040200u));
-  r[1] = static_cast<int>(__builtin_amdgcn_perm(static_cast<uint32_t>(e[3]), static_cast<uint32_t>(e[1]), 0x06040200u));
-  r[2] = static_cast<int>(__builtin_amdgcn_perm(static_cast<uint32_t>(e[2]), static_cast<uint32_t>(e[0]), 0x07050301u));
-  r[3] = static_cast<int>(__builtin_amdgcn_perm(static_cast<uint32_t>(e[3]), static_cast<uint32_t>(e[1]), 0x07050301u));
-  return r;
-}
 
 // BM: activation rows per block tile, 128 or 112 (seven 16-row fragments,
 // for shapes whose 128-row tiles leave the last round of blocks mostly
@@ -427,7 +402,10 @@ hipError_t launch_w4a4_gemm(Epilogue epi, const uint8_t* qx, const float* sx, in
   if (e != hipSuccess) return e;
   e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
-  const int bm = gemm_tile_rows(M, N, 2 * std::max<int64_t>(kNumXcd, cus / kNumXcd * kNumXcd));
+  const int64_t slots = std::max<int64_t>(kNumXcd, cus / kNumXcd * kNumXcd);
+  if (const int tile = gemm_narrow_tile(M, N, K, wf, slots))
+    return launch_gemm_narrow(tile, epi, qx, sx, M, K, qw, sw, N, bias, out, st, wf);
+  const int bm = gemm_tile_rows(M, N, 2 * slots);
   const int tiles_m = static_cast<int>((M + bm - 1) / bm);
   const int tiles_n = static_cast<int>((N + kBN - 1) / kBN);
   const int64_t T = static_cast<int64_t>(tiles_m) * tiles_n;

@@ -20,6 +20,7 @@ constexpr int kThreads = 256;                 // four waves per block
 constexpr int kGroupM = 8;                    // m-tiles per n sweep in the tile order
 constexpr int kNumXcd = 8;                    // MI355X accelerator complex dies
 constexpr int kBufferFlags = 0x00020000;      // buffer descriptor word 3 for raw byte-addressed loads
+constexpr uint32_t kOutsideOperand = 0x80000000u;  // a buffer offset past every operand: loads read as zero
 constexpr int kWaitVm0 = (0x7 << 4) | (0xF << 8);  // s_waitcnt vmcnt(0), other counters untouched
 
 static_assert(kChunks == 4 && kXChunks == 8, "swizzles below assume 4 packed / 8 int8 chunks per LDS row");
@@ -40,6 +41,31 @@ __device__ __forceinline__ v4i unpack8(uint32_t p0, uint32_t p1) {
   r[1] = static_cast<int>(p0 & 0xF0F0F0F0u);
   r[2] = static_cast<int>((p1 << 4) & 0xF0F0F0F0u);
   r[3] = static_cast<int>(p1 & 0xF0F0F0F0u);
+  return r;
+}
+
+// Widen 16 ternary codes (one packed dword, code i in bits 2i .. 2i+1) to
+// int8 64 * code: dword d, byte b of the result holds code 4b + d.  Shifting
+// a 2-bit field to the top of its byte sign-extends it for free.
+__device__ __forceinline__ v4i unpack_tern(uint32_t p) {
+  v4i r;
+  r[0] = static_cast<int>((p << 6) & 0xC0C0C0C0u);
+  r[1] = static_cast<int>((p << 4) & 0xC0C0C0C0u);
+  r[2] = static_cast<int>((p << 2) & 0xC0C0C0C0u);
+  r[3] = static_cast<int>(p & 0xC0C0C0C0u);
+  return r;
+}
+
+// Widen 16 int4 activation codes (p0: codes 0..7, p1: codes 8..15) into the
+// order unpack_tern produces: dword d, byte b = 16 * code 4b + d.
+__device__ __forceinline__ v4i unpack8_tern_order(uint32_t p0, uint32_t p1) {
+  const v4i e = unpack8(p0, p1);  // e[0] = codes 0 2 4 6, e[1] = 1 3 5 7, e[2] = 8 10 12 14, e[3] = 9 11 13 15
+  v4i r;
+  // v_perm_b32: selector byte values 0..3 pick the second operand's bytes, 4..7 the first's.
+  r[0] = static_cast<int>(__builtin_amdgcn_perm(static_cast<uint32_t>(e[2]), static_cast<uint32_t>(e[0]), 0x06040200u));
+  r[1] = static_cast<int>(__builtin_amdgcn_perm(static_cast<uint32_t>(e[3]), static_cast<uint32_t>(e[1]), 0x06040200u));
+  r[2] = static_cast<int>(__builtin_amdgcn_perm(static_cast<uint32_t>(e[2]), static_cast<uint32_t>(e[0]), 0x07050301u));
+  r[3] = static_cast<int>(__builtin_amdgcn_perm(static_cast<uint32_t>(e[3]), static_cast<uint32_t>(e[1]), 0x07050301u));
   return r;
 }
 

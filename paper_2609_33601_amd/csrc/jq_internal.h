@@ -42,6 +42,14 @@ hipError_t launch_w4a4_gemm(Epilogue epi, const uint8_t* qx, const float* sx, in
 // `slots` block slots (two per CU).
 int gemm_tile_rows(int64_t M, int64_t N, int64_t slots);
 
+// Its kernel for products with few output tiles: which of its tiles an M x K
+// by K x N product on `cus` CUs takes (0: none, it goes to the tiled kernel),
+// and its launch.
+int gemm_narrow_tile(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus);
+hipError_t launch_gemm_narrow(int tile, Epilogue epi, const uint8_t* qx, const float* sx, int64_t M, int64_t K,
+                              const uint8_t* qw, const float* sw, int64_t N, const uint16_t* bias, void* out,
+                              hipStream_t st, WeightFormat wf);
+
 // Group-wise GEMM: scales sx [M, K/G] and sw [N, K/G]; epi is kBf16 or kF32.
 hipError_t launch_w4a4g_gemm(Epilogue epi, const uint8_t* qx, const float* sx, int64_t M, int64_t K, int G,
                              const uint8_t* qw, const float* sw, int64_t N, const uint16_t* bias, void* out,
