@@ -663,17 +663,20 @@ __device__ __forceinline__ RawRsrc raw_rsrc(const void* base, uint32_t bytes) {
                static_cast<uint32_t>(kBufferFlags)};
   return r;
 }
-// The LDS byte address of a __shared__ object: the low 32 bits of its generic address.
+// The LDS byte address of a __shared__ object.
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p));
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const lds_void_t*)p));
 }
 __device__ __forceinline__ void dma16_raw(const RawRsrc& r, uint32_t lds, uint32_t voffset, uint32_t soffset) {
   asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voffset), "s"(r.w), "s"(soffset) : "memory");
 }
+// 16 bytes per lane at voffset + soffset + OFFSET (an instruction immediate).
+template <int OFFSET>
 __device__ __forceinline__ v4i32 load16_raw(const RawRsrc& r, uint32_t voffset, uint32_t soffset) {
   v4i32 v;
-  asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen" : "=v"(v) : "v"(voffset), "s"(r.w), "s"(soffset));
+  asm volatile("buffer_load_dwordx4 %0, %1, %2, %3 offen offset:%4"
+               : "=v"(v) : "v"(voffset), "s"(r.w), "s"(soffset), "n"(OFFSET));
   return v;
 }
 __device__ __forceinline__ void dma4_raw(const RawRsrc& r, uint32_t lds, uint32_t voffset) {
@@ -756,15 +759,6 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
   // the band's stage.  Bands past the operand are clamped (their results are
   // discarded); bands past the tile get an offset outside the operand, which
   // the buffer load answers with zeros without touching memory.
-  int rband[kDmaPerWave];
-  uint32_t rpart[kDmaPerWave];
-#pragma unroll
-  for (int j = 0; j < kDmaPerWave; ++j) {
-    const int Q = 64 * (kDmaPerWave * wave + j) + lane;
-    const int R = Q / 96, q = Q % 96;
-    rband[j] = R % S::kBands;
-    rpart[j] = (R % S::kBands) < tile_bands ? (R / S::kBands) * kFragBytes + 16 * q : kOutside;
-  }
   const uint32_t band_bytes = static_cast<uint32_t>(ksteps) * kFragBytes;
   // The blocks walk the stages of their tiles from a point of K of their
   // own (the fp32 sums of integers do not depend on the order).  One block
@@ -777,22 +771,47 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
   const int koff =
       WAVES == 8 ? static_cast<int>(blockIdx.x % kNumXcd) * T / kNumXcd
                  : ((static_cast<int>(blockIdx.x / kNumXcd) >= grid_blocks / kNumXcd / 2) ? T / 2 : 0);
-  auto rot = [&](int st) __attribute__((always_inline)) { return st + koff < T ? st + koff : st + koff - T; };
-
-  // Stage `st` of the tile at (m0, n0): part j of the wave's share of its
-  // activations into slot k, or part pp (band pp / 3, 16-byte part pp % 3)
-  // of its weights into w.
-  auto issue_dma = [&](int m0, int st, int k, int j) __attribute__((always_inline)) {
-    uint4* dst = slot(k) + 64 * kDmaPerWave * wave;
-    const uint32_t band = static_cast<uint32_t>(min(m0 / 32 + rband[j], mbands - 1));
-    dma16_raw(rsx, lds_addr(dst + 64 * j), rpart[j] == kOutside ? kOutside : band * band_bytes + rpart[j],
-              2 * kFragBytes * rot(st));
+  // So the byte offset of a stage within its band just counts on, modulo the
+  // band, through all the block's tiles.
+  auto next_k = [&](uint32_t ko) __attribute__((always_inline)) {
+    ko += 2 * kFragBytes;
+    return ko == band_bytes ? 0u : ko;
   };
-  auto load_w = [&](WRaw& w, int n0, int st, int pp) __attribute__((always_inline)) {
-    const int f = pp / 3, q = pp % 3;
-    const uint32_t wb = static_cast<uint32_t>(min(n0 / 32 + 2 * wn + f, nbands - 1)) * band_bytes;
-    const uint32_t so = static_cast<uint32_t>(2 * rot(st) * kFragBytes);
-    w.p[f][q] = load16_raw(rsw, wb + 1024 * q + 16 * lane, so);
+
+  // Addresses are kept, not computed per load: a wave issues an instruction
+  // every four clocks or so, so scalar and vector arithmetic between the
+  // MFMAs costs as much as the loads it serves.  A tile's DMA offsets are
+  // three registers per lane, its weight bands two scalars.
+  auto dma_offsets = [&](int m0, uint32_t* v) __attribute__((always_inline)) {
+    // (the lane index through an empty asm: computed here, once a tile, not
+    // kept in registers that the stages need)
+    int l = threadIdx.x & 63;
+    asm volatile("" : "+v"(l));
+#pragma unroll
+    for (int j = 0; j < kDmaPerWave; ++j) {
+      const int Q = 64 * (kDmaPerWave * wave + j) + l;
+      const int R = Q / 96, q = Q % 96;
+      const uint32_t band = static_cast<uint32_t>(min(m0 / 32 + R % S::kBands, mbands - 1));
+      v[j] = R % S::kBands < tile_bands ? band * band_bytes + (R / S::kBands) * kFragBytes + 16 * q : kOutside;
+    }
+  };
+  auto w_bases = [&](int n0, uint32_t* b) __attribute__((always_inline)) {
+#pragma unroll
+    for (int f = 0; f < 2; ++f) b[f] = static_cast<uint32_t>(min(n0 / 32 + 2 * wn + f, nbands - 1)) * band_bytes;
+  };
+  uint32_t slot_at[3];  // where the wave's share of each slot starts
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+    slot_at[k] = __builtin_amdgcn_readfirstlane(lds_addr(slot(k))) + 16 * 64 * kDmaPerWave * wave;
+  // Part j of the wave's share of a stage's activations (offset v, stage at
+  // ko) into slot k; 16-byte part pp % 3 of weight band pp / 3 into w.
+  auto issue_dma = [&](uint32_t v, uint32_t ko, int k, int j) __attribute__((always_inline)) {
+    dma16_raw(rsx, slot_at[k] + 16 * 64 * j, v, ko);
+  };
+  const uint32_t lane16 = 16 * lane;
+  auto load_w = [&](WRaw& w, uint32_t at0, uint32_t at1, auto PP) __attribute__((always_inline)) {
+    constexpr int f = decltype(PP)::value / 3, q = decltype(PP)::value % 3;
+    w.p[f][q] = load16_raw<1024 * q>(rsw, lane16, f ? at1 : at0);
   };
   // The MFMA operands of a loaded stage, once the wait for its loads has
   // passed.  The compiler takes an asm load's result as ready when the asm
@@ -870,34 +889,31 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
   // The block walks one stream of stages g = i * T + t over its tiles i.
   // Loads run ahead across tile boundaries: the weights of stage g + 1 and
   // the activations of stage g + 3.  Past the block's last stage they are
-  // issued anyway, for its last stage again (every address stays inside the
+  // issued anyway, for its last tile again (every address stays inside the
   // operands), which keeps the wait counts below constant.
   int cm0, cn0, xm0, xn0;  // current and next tile
   tile_at(0, &cm0, &cn0);
   if (ntiles > 1) tile_at(1, &xm0, &xn0);
   else xm0 = cm0, xn0 = cn0;
-  // Tile and stage of g + k for k < 2T, clamped to the block's last stage.
-  auto ahead = [&](int t, int ti, int k, int* m0, int* n0, int* st) __attribute__((always_inline)) {
-    const int u = t + k;
-    if (u < T) {
-      *m0 = cm0, *n0 = cn0, *st = u;
-    } else if (ti + 1 < ntiles) {
-      *m0 = xm0, *n0 = xn0, *st = min(u - T, last);
-    } else {
-      *m0 = cm0, *n0 = cn0, *st = last;
-    }
-  };
+  uint32_t cv[kDmaPerWave], xv[kDmaPerWave];  // the DMA offsets of the current and the next tile
+  uint32_t cb[2], xb[2];     // the weight bands of the current and the next tile
+  dma_offsets(cm0, cv);
+  dma_offsets(xm0, xv);
+  w_bases(cn0, cb);
+  w_bases(xn0, xb);
+  uint32_t kw = 2 * kFragBytes * static_cast<uint32_t>(koff), kd = kw;  // stages of the next weight load and DMA
 
   WRaw w0, w1;
-  {
-    int m0, n0, st;
-    static_for<kWLoads>([&](auto PP) __attribute__((always_inline)) { load_w(w0, cn0, 0, decltype(PP)::value); });
-    static_for<kDmaPerWave>([&](auto J) __attribute__((always_inline)) { issue_dma(cm0, 0, 0, decltype(J)::value); });
-    ahead(0, 0, 1, &m0, &n0, &st);
-    static_for<kDmaPerWave>([&](auto J) __attribute__((always_inline)) { issue_dma(m0, st, 1, decltype(J)::value); });
-    ahead(0, 0, 2, &m0, &n0, &st);
-    static_for<kDmaPerWave>([&](auto J) __attribute__((always_inline)) { issue_dma(m0, st, 2, decltype(J)::value); });
-  }
+  // A tile of fewer than three stages is the block's only one: its DMA goes
+  // round K again, into slots that are never read.
+  static_for<kWLoads>([&](auto PP) __attribute__((always_inline)) { load_w(w0, cb[0] + kw, cb[1] + kw, PP); });
+  kw = next_k(kw);
+  static_for<3>([&](auto K_) __attribute__((always_inline)) {
+    static_for<kDmaPerWave>([&](auto J) __attribute__((always_inline)) {
+      issue_dma(cv[decltype(J)::value], kd, decltype(K_)::value, decltype(J)::value);
+    });
+    kd = next_k(kd);
+  });
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kDmaPerWave));  // DMA(0)
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
@@ -1064,8 +1080,8 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
   auto stage = [&](auto I) __attribute__((always_inline)) {
     constexpr int i = decltype(I)::value;
     constexpr int cur = i % 3, nxt = (i + 1) % 3;
-    int wm0, wn0, wst, dm0 = 0, dst = 0;  // the tile and stage of the weights and the DMA issued here
-    ahead(t, ti, 1, &wm0, &wn0, &wst);
+    const bool end = t == last;
+    const uint32_t at0 = (end ? xb[0] : cb[0]) + kw, at1 = (end ? xb[1] : cb[1]) + kw;  // stage g + 1's weights
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(kDmaPerWave));
     __builtin_amdgcn_sched_barrier(0);
     const WFrag wc = frags(*wset[i % 2]);
@@ -1081,11 +1097,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
       if constexpr (ks == 0) {
         // weight parts pp with pp nfm / kWLoads == j
         static_for<kWLoads>([&](auto PP) __attribute__((always_inline)) {
-          constexpr int pp = decltype(PP)::value;
-          if constexpr (pp * nfm / kWLoads == j) load_w(*wset[(i + 1) % 2], wn0, wst, pp);
+          if constexpr (decltype(PP)::value * nfm / kWLoads == j) load_w(*wset[(i + 1) % 2], at0, at1, PP);
         });
       } else if constexpr (fm < kDmaPerWave) {
-        issue_dma(dm0, dst, cur, fm);
+        issue_dma(t + 3 < T ? cv[fm] : xv[fm], kd, cur, fm);
       }
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (j == nfm - 1) {
@@ -1094,10 +1109,10 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         if (t == 0) issue_scales(cm0, cn0);
-        int dn0;
-        ahead(t, ti, 3, &dm0, &dn0, &dst);
       }
     });
+    kw = next_k(kw);
+    kd = next_k(kd);
     // (past the block's last stage the reads of the next slot are of data
     // that is not used)
     static_assert(kDmaPerWave <= 3, "the DMA parts go with the second k-step's fragments");
@@ -1112,7 +1127,14 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
       ++ti;
       t = 0;
       cm0 = xm0, cn0 = xn0;
-      if (ti + 1 < ntiles) tile_at(ti + 1, &xm0, &xn0);
+      cb[0] = xb[0], cb[1] = xb[1];
+      if (ti + 1 < ntiles) {
+        tile_at(ti + 1, &xm0, &xn0);
+        w_bases(xn0, xb);
+      }
+#pragma unroll
+      for (int j = 0; j < kDmaPerWave; ++j) cv[j] = xv[j];
+      dma_offsets(xm0, xv);
     } else {
       ++t;
     }
