@@ -493,13 +493,14 @@ jq_status jq_w4a4_f6_gemm_i32(const void* xf6, int64_t M, int64_t K,
 jq_status jq_gemm_plan(int64_t M, int64_t N, int64_t K, int cus, int* tile_rows);
 
 /*
- * The block shape the BF6 GEMM (jq_w4a4_f6_gemm, _linear, _gemm_i32) takes for
- * an M x K by K x N product on a device with `cus` compute units, for checking
- * and tuning: *waves = 8 (one 8-wave block per CU) or 4 (two 4-wave blocks per
- * CU), *tile_rows = the rows of activations per output tile (256 columns).
- * Products with too few such tiles to fill the device (few tokens, narrow
- * weights) take a kernel of smaller tiles instead; the plan is then the one
- * they would have had.
+ * The nominal block shape of the BF6 GEMM (jq_w4a4_f6_gemm, _linear, _gemm_i32)
+ * for an M x K by K x N product on a device with `cus` compute units, by which
+ * products can be told apart in checks and tuning: *waves = 8 (one large tile
+ * per CU at a time) or 4 (two small ones), *tile_rows = the rows of activations
+ * per output tile (256 columns).  The kernels that run refine it: tiles of 128
+ * to 256 rows by the least estimated time, and smaller ones for products with
+ * too few of those to fill the device (few tokens, narrow weights).  The plan
+ * does not report that choice, and the results do not depend on it.
  * Host-only; launches nothing.
  * Errors: JQ_ERR_INVALID_ARG, JQ_ERR_UNSUPPORTED_SHAPE.
  */

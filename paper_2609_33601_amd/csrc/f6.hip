@@ -1,4 +1,4 @@
-// The W4A4 layer on gfx950's 6-bit matrix cores (v_mfma_scale_f32_32x32x64_f8f6f4
+// The W4A4 layer on gfx950's 6-bit matrix cores (v_mfma_f32_32x32x64_f8f6f4
 // with BF6 = E3M2 operands), an exact alternative to the int8 MFMA path.
 //
 // Why it is exact.  Every int4 code -8..7 is a BF6 E3M2 value (|c| = 1.m * 2^e
@@ -46,61 +46,60 @@
 //     whatever its width).
 //
 // GEMM structure.  (Products with few output tiles go to f6_narrow.hip.)
-// Persistent blocks walk the output tiles (256 n columns
-// each) in an XCD-aware order, in one of two shapes:
-//   * one 8-wave block per CU (two waves per SIMD) on tiles of
-//     32 * tile_bands rows, tile_bands 7 or 8 picked per shape to spread the
-//     tiles evenly over the CUs.  Wave (wm, wn) owns weight bands 2wn,
-//     2wn + 1 of the tile and the activation bands of half wm (four bands,
-//     or tile_bands - 4 in the second half; the two waves on a SIMD belong
-//     to different halves, so every SIMD gets the same work).  Each XCD's
-//     blocks walk K from stage x T / 8 of it (XCD x) round to it, so that
-//     the eight XCDs read different slices of the operands at any moment
-//     (FLUX MLP-down in the benchmark step: 157 -> 145 us);
-//   * two 4-wave blocks per CU on tiles of 128 rows, wave wn owning weight
-//     bands 2wn, 2wn + 1 and all four activation bands.  Taken where 256-row
-//     tiles would not cover M evenly and K is not long: each block's epilogue
-//     then runs beside the other block's MFMAs.  So that the two blocks of a
-//     CU stay out of step, the blocks in the second half of each XCD's share
+// Persistent blocks of four waves walk the output tiles, 32 NFM rows x 256
+// columns each, in an XCD-aware order.  Wave w owns weight bands 2w, 2w + 1 of
+// the tile and all NFM activation bands: 2 x NFM tiles of 32x32.  f6_tile_bands
+// picks, by the least estimated time,
+//   * NFM = 5 .. 8 with one block per CU, one wave per SIMD and up to 256
+//     accumulators per lane.  Each XCD's blocks walk K from stage x T / 8 of
+//     it (XCD x) round to it, so that the eight XCDs read different slices of
+//     the operands at any moment;
+//   * NFM = 4 with two blocks per CU, which re-reads the operands more but
+//     runs one block's epilogue beside the other's MFMAs.  So that the two
+//     stay out of step, the blocks in the second half of each XCD's share
 //     walk K from its middle stage round to it (the sum is exact in any
 //     order).
-// Either way a wave holds up to 2 x 4 tiles of 32x32, 128 fp32 accumulators
-// per lane.
-//   * Activations: shared by the four waves that read the same bands, staged
-//     through LDS.  A stage is 128 codes of K (two k-steps x the block's
-//     activation bands: 16 fragments, 24 KiB, or 8 fragments, 12 KiB),
-//     moved by buffer_load ... lds (no registers) into a ring of three stage
-//     slots, three stages ahead.
+// What bounds it.  A stage (128 codes of K) of a 256 x 256 tile is 32 MFMAs
+// per SIMD, 1024 clocks, and 48 KiB of operands that pass the CU's vector
+// memory path at 64 bytes per clock, 768 clocks.  With eight waves per block,
+// four bands each, the two waves of a SIMD loaded the same weights twice (72
+// KiB, 1152 clocks) and every wave had half the MFMAs to hide its other
+// instructions under; the stage took 0.72 us and takes 0.59 us now:
+// 4096 x 12288 -> 4096 74 -> 66 us, 9216 x 12288 -> 3072 139 -> 119 us.  One
+// wave gives an XCD four tile heights, since no second wave has to have the
+// same work: 6000 x 12288 -> 4096 in 192-row tiles 158 -> 137 us, 4608 x 8192
+// -> 1024 in 160-row tiles 50 -> 36 us.
+// The rest is the stages' own stalls and the epilogue: about 4 us a tile at
+// NFM = 8, its vector arithmetic (two multiplies and half a conversion per
+// output, 256 outputs a lane) with only one wave per SIMD to run it.
+//   * Activations: shared by the four waves, staged through LDS.  A stage is
+//     3 KiB per band, consecutive in memory, moved by buffer_load ... lds (no
+//     registers) into a ring of three stage slots, three stages ahead.
 //   * Weights: loaded straight into registers one stage ahead, two register
-//     sets (so the stage loop is unrolled by six, a multiple of both ring
-//     sizes).
-//   * Per stage: the eight MFMAs of k-step 0 run while the wave reads its
-//     k-step 1 fragments from LDS and issues the next stage's weight loads,
-//     one or two after each fragment's MFMAs; then it waits for its share
-//     of the next stage's DMA and meets the others at a barrier (no memory
-//     fence); then the MFMAs of k-step 1 run while the next stage's k-step 0
+//     sets (so the stage loop is unrolled by two; a tile with an odd number
+//     of stages moves the loaded set over at its end).
+//   * Per stage: the MFMAs of k-step 0 run while the wave reads its k-step 1
+//     fragments from LDS and issues the next stage's weight loads, one after
+//     each of the first fragments' MFMAs; then it waits for its share of the
+//     next stage's DMA and meets the others at a barrier (no memory fence);
+//     then the MFMAs of k-step 1 run while the next stage's k-step 0
 //     fragments are read and the DMA three stages ahead goes into the slot
-//     just read, one instruction after each of the first fragments.  Issued
-//     in one burst per wave at the stage's start and middle, the same loads
-//     queued up behind each other and held the waves' MFMAs back (the
-//     spread issue took the FLUX MLP-down GEMM from 147 to 131 us on zero
-//     codes).  No VALU work sits between the MFMAs.
+//     just read.  Issued in one burst, the same loads queue up behind each
+//     other and hold the MFMAs back.  No arithmetic on vectors sits between
+//     the MFMAs, and every address is scalar.
 //   * Every vector-memory instruction of the stage loop (the weight loads
 //     and the buffer -> LDS transfers) is issued as an instruction of its
-//     own, and the loop orders it with explicit waits only: at a stage's
-//     start, vmcnt(3) (this stage's weights, issued before the previous
-//     stage's DMA, have landed); at its middle, vmcnt(9), lgkmcnt(0) and the
-//     barrier (the next slot's DMA has landed and every read of the slot
-//     about to be refilled has completed).  Left to the compiler, the
-//     transfers made it wait for every DMA in flight before each LDS read.
-//     The compiler does not know that these loads complete after they
-//     issue, so the loaded registers pass through an empty asm after their
-//     wait before any use, and the build checks the generated code: no
-//     instruction may touch a load's registers before a wait retires it
-//     (check_waits.py).  The file is also built without machine sinking,
-//     which otherwise moved the first k-step's MFMAs below the stage's
-//     barrier (into the block after the tile's first-stage branch), leaving
-//     the matrix pipes idle while both waves of a SIMD waited there.
+//     own, and the loop orders it with explicit waits only (see the stage).
+//     Left to the compiler, the transfers made it wait for every DMA in
+//     flight before each LDS read.  The compiler does not know that these
+//     loads complete after they issue, so the loaded registers pass through
+//     an empty asm after their wait before any use, and the build checks the
+//     generated code: no instruction may touch a load's registers before a
+//     wait retires it (check_waits.py).  The file is also built without
+//     machine sinking, which otherwise moved the first k-step's MFMAs below
+//     the stage's barrier.
+//   * The matrix instruction is the one without scales (mfma_bf6): with them
+//     it is 2-4% slower in this loop.
 //   * An activation fragment's 16- and 8-byte parts land next to each other
 //     in registers (the 8-byte part read on its own, not paired with another
 //     fragment's), and a band's three 16-byte weight parts of a stage are
@@ -135,23 +134,9 @@ typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h32 __attribute__((ext_vector_type(32)));
 typedef unsigned v4u32 __attribute__((ext_vector_type(4)));
 
-constexpr int kFBN = 256;                 // block tile columns
-constexpr int kDmaPerWave = 3;            // stage DMA instructions per wave
-constexpr int64_t kShortK = 6144;          // largest K that may take the two-block shape
-
-// The GEMM comes in two block shapes (WAVES = 8 or 4 waves of 64): one
-// 8-wave block per CU on a tile of up to 256 activation rows, or two 4-wave
-// blocks per CU on tiles of 128 rows.  Per wave the work is the same (two
-// weight bands, four activation bands); a stage holds the block's
-// activation bands for two k-steps.
-template <int WAVES>
-struct F6Shape {
-  static constexpr int kThreads = 64 * WAVES;
-  static constexpr int kBands = WAVES;                          // activation bands staged per tile
-  static constexpr int kFBM = 32 * kBands;                      // tile rows at most
-  static constexpr int kStageU4 = 2 * kBands * kFragBytes / 16;  // one stage slot, 16-byte units
-  static_assert(kStageU4 == 64 * kDmaPerWave * WAVES, "a stage is 3 DMA instructions per wave");
-};
+constexpr int kFBN = 256;    // block tile columns of the GEMM
+constexpr int kF6Waves = 4;  // waves of a GEMM block
+constexpr int kWLoads = 6;   // weight loads per wave and stage
 
 // 32 codes (as exact fp32 integers, code p in q[p]) -> six dwords, code p in bits 6p..6p+5.
 // The converter interleaves its two sources (field 2i <- src0[i], field 2i+1 <- src1[i]).
@@ -667,9 +652,12 @@ __device__ __forceinline__ RawRsrc raw_rsrc(const void* base, uint32_t bytes) {
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const lds_void_t*)p));
 }
+// OFFSET (an instruction immediate) moves both the source and the target.
+template <int OFFSET = 0>
 __device__ __forceinline__ void dma16_raw(const RawRsrc& r, uint32_t lds, uint32_t voffset, uint32_t soffset) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voffset), "s"(r.w), "s"(soffset) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
+               :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voffset), "s"(r.w), "s"(soffset), "n"(OFFSET)
+               : "memory");
 }
 // 16 bytes per lane at voffset + soffset + OFFSET (an instruction immediate).
 template <int OFFSET>
@@ -687,46 +675,34 @@ __device__ __forceinline__ void dma4_raw(const RawRsrc& r, uint32_t lds, uint32_
 constexpr int kWaitcntBase = (0x7 << 4) | (0xF << 8);  // expcnt, lgkmcnt: no wait
 constexpr int vmcnt_imm(int n) { return kWaitcntBase | (n & 0xF) | ((n >> 4) << 14); }
 constexpr int kLgkm0 = 0xC07F;                          // lgkmcnt(0), vmcnt and expcnt: no wait
-constexpr int kWLoads = 6;                              // weight loads per wave per stage
-
-// BIAS_TAIL: a bias with odd N, whose last value the epilogue of a ragged
-// tile reads from memory (its staged pair reads past the buffer as zero);
-// otherwise every bias value comes from LDS and the epilogue has no branch.
-template <int WAVES, Epilogue EPI, bool HAS_BIAS, bool BIAS_TAIL>
-__global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
+// One wave's share of a tile is two weight bands and all NFM activation bands;
+// PER_CU blocks share a CU.
+//
+// BIAS_TAIL: a bias with odd N, whose last value the epilogue reads from memory
+// (its staged pair reads past the buffer as zero).
+template <int NFM, int PER_CU, Epilogue EPI, bool HAS_BIAS, bool BIAS_TAIL>
+__global__ __launch_bounds__(64 * kF6Waves, PER_CU) void w4a4_f6_gemm_kernel(
     const uint8_t* __restrict__ xf6, const float* __restrict__ sx, int M, int mbands,
     const uint8_t* __restrict__ wf6, const float* __restrict__ sw, int N, int nbands, int ksteps,
-    const uint16_t* __restrict__ bias, void* __restrict__ out, int tile_bands, int tiles_m, int tiles_n,
-    int grid_blocks) {
-  // The ring (72 or 36 KiB) as three separate arrays.  With the stage loop
-  // unrolled by six every slot is known at compile time, so the compiler
-  // can tell the slot being read from the one the DMA is writing.
-  using S = F6Shape<WAVES>;
-  constexpr int kStageU4 = S::kStageU4, kFBM = S::kFBM, kF6Threads = S::kThreads;
-  __shared__ uint4 lds0[kStageU4];
-  __shared__ uint4 lds1[kStageU4];
-  __shared__ uint4 lds2[kStageU4];
-  // Output staging for the epilogue: per wave 64 rows x 64 bf16 (128 bytes a
-  // row), 16-byte chunk c of row r at chunk c ^ ((r >> 1) & 7).  Accessed
-  // only as stg[i] / stg2[i] with a computed index, so that every access
-  // keeps the alias information that tells it apart from the DMA targets
-  // (an access without it would wait for every load in flight).
-  __shared__ v4u32 stg[kF6Threads / 64 * 512];
+    const uint16_t* __restrict__ bias, void* __restrict__ out, int tiles_m, int tiles_n, int grid_blocks) {
+  constexpr int kOwn = (NFM + kF6Waves - 1) / kF6Waves;  // activation bands a wave moves
+  constexpr int kDma = 3 * kOwn;                         // DMA instructions per wave and stage
+  constexpr int kUnit = 2 * kFragBytes;                  // a band's bytes of a stage, in memory and in LDS
+  constexpr uint32_t kSlot = kF6Waves * kOwn * kUnit;
+  constexpr int kRows = 32 * NFM;
+  constexpr int kScX = (kRows + 63) / 64 * 64;
+  __shared__ __align__(16) uint8_t ring[3 * kSlot];
+  // Output staging for the epilogue: per wave two buffers of 32 rows x 64
+  // bf16, 16-byte chunk c of row r at chunk c ^ ((r >> 1) & 7).
+  __shared__ __align__(16) uint8_t stg[kF6Waves * 8192];
   // The current tile's scales and bias, moved in by DMA for the epilogue.
-  __shared__ float sc_x[kFBM];
+  __shared__ float sc_x[kScX];
   __shared__ float sc_w[kFBN];
   __shared__ float sc_b[kFBN / 2];  // bf16 pairs
-  auto slot = [&](int k) __attribute__((always_inline)) { return k == 0 ? lds0 : (k == 1 ? lds1 : lds2); };
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = WAVES == 8 ? wave >> 2 : 0, wn = wave & 3;  // activation half, weight quarter (2 bands)
-  // A tile has tile_bands (7 or 8) bands of 32 activation rows: the first
-  // half takes four of them, the second half the rest, so each SIMD (one wave
-  // of each half) does the same work whatever the tile height.
-  const int tile_rows = 32 * tile_bands;
-  const int T = ksteps / 2;                  // stages of 128 codes per tile
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int T = ksteps / 2;  // stages of 128 codes per tile
   const int last = T - 1;
 
   // The block's tiles: virtual block ids v = blockIdx.x + i * grid_blocks of
@@ -742,24 +718,34 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
     for (int v = blockIdx.x; v < vmax && tile_of_block(v, tiles_m, tiles_n, &tc); v += grid_blocks) ++ntiles;
   }
   if (ntiles == 0) return;
-  auto tile_at = [&](int i, int* m0, int* n0) __attribute__((always_inline)) {
-    TileCoord tc;
-    tile_of_block(blockIdx.x + i * grid_blocks, tiles_m, tiles_n, &tc);
-    *m0 = tc.tm * tile_rows;
-    *n0 = tc.tn * kFBN;
-  };
 
   const RawRsrc rsx = raw_rsrc(xf6, static_cast<uint32_t>(static_cast<int64_t>(mbands) * ksteps * kFragBytes));
   const RawRsrc rsw = raw_rsrc(wf6, static_cast<uint32_t>(static_cast<int64_t>(nbands) * ksteps * kFragBytes));
-
-  // Activation DMA: the 16 fragments of a stage ((k-step s, band b) in order
-  // 8s + b) are contiguous 1536-byte blocks in LDS; slot part
-  // Q = 64 (3 wave + j) + lane of the stage is byte 16 (Q % 96) of fragment
-  // Q / 96.  Per lane: the band within the tile and the byte offset within
-  // the band's stage.  Bands past the operand are clamped (their results are
-  // discarded); bands past the tile get an offset outside the operand, which
-  // the buffer load answers with zeros without touching memory.
   const uint32_t band_bytes = static_cast<uint32_t>(ksteps) * kFragBytes;
+
+  // A tile and the wave's bands in it, as byte offsets: the activation bands
+  // it moves to LDS and the weight bands it owns (bands past the operand are
+  // clamped; their results are discarded).  Everything is scalar: a wave
+  // issues an instruction every four clocks or so, so arithmetic between the
+  // MFMAs costs as much as the loads it serves.
+  struct Tile {
+    int m0, n0;
+    uint32_t x[kOwn], w[2];
+  };
+  auto tile_at = [&](int i) __attribute__((always_inline)) {
+    TileCoord tc;
+    tile_of_block(blockIdx.x + i * grid_blocks, tiles_m, tiles_n, &tc);
+    Tile r;
+    r.m0 = tc.tm * kRows;
+    r.n0 = tc.tn * kFBN;
+#pragma unroll
+    for (int f = 0; f < kOwn; ++f)
+      r.x[f] = static_cast<uint32_t>(min(r.m0 / 32 + kOwn * wave + f, mbands - 1)) * band_bytes;
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+      r.w[f] = static_cast<uint32_t>(min(r.n0 / 32 + 2 * wave + f, nbands - 1)) * band_bytes;
+    return r;
+  };
   // The blocks walk the stages of their tiles from a point of K of their
   // own (the fp32 sums of integers do not depend on the order).  One block
   // per CU: each XCD starts an eighth of K after the one before, so that at
@@ -767,60 +753,43 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
   // all requesting the same weight lines together.  Two blocks per CU: the
   // second half of each XCD's blocks starts from the middle of K, so the two
   // blocks on a CU reach their epilogues half a tile apart and one runs its
-  // MFMAs while the other stores.
+  // MFMAs while the other stores.  The byte offset of a stage within its
+  // band just counts on, modulo the band, through all the block's tiles.
   const int koff =
-      WAVES == 8 ? static_cast<int>(blockIdx.x % kNumXcd) * T / kNumXcd
-                 : ((static_cast<int>(blockIdx.x / kNumXcd) >= grid_blocks / kNumXcd / 2) ? T / 2 : 0);
-  // So the byte offset of a stage within its band just counts on, modulo the
-  // band, through all the block's tiles.
+      PER_CU == 1 ? static_cast<int>(blockIdx.x % kNumXcd) * T / kNumXcd
+                  : ((static_cast<int>(blockIdx.x / kNumXcd) >= grid_blocks / kNumXcd / 2) ? T / 2 : 0);
   auto next_k = [&](uint32_t ko) __attribute__((always_inline)) {
-    ko += 2 * kFragBytes;
+    ko += kUnit;
     return ko == band_bytes ? 0u : ko;
   };
 
-  // Addresses are kept, not computed per load: a wave issues an instruction
-  // every four clocks or so, so scalar and vector arithmetic between the
-  // MFMAs costs as much as the loads it serves.  A tile's DMA offsets are
-  // three registers per lane, its weight bands two scalars.
-  auto dma_offsets = [&](int m0, uint32_t* v) __attribute__((always_inline)) {
-    // (the lane index through an empty asm: computed here, once a tile, not
-    // kept in registers that the stages need)
-    int l = threadIdx.x & 63;
-    asm volatile("" : "+v"(l));
-#pragma unroll
-    for (int j = 0; j < kDmaPerWave; ++j) {
-      const int Q = 64 * (kDmaPerWave * wave + j) + l;
-      const int R = Q / 96, q = Q % 96;
-      const uint32_t band = static_cast<uint32_t>(min(m0 / 32 + R % S::kBands, mbands - 1));
-      v[j] = R % S::kBands < tile_bands ? band * band_bytes + (R / S::kBands) * kFragBytes + 16 * q : kOutside;
-    }
-  };
-  auto w_bases = [&](int n0, uint32_t* b) __attribute__((always_inline)) {
-#pragma unroll
-    for (int f = 0; f < 2; ++f) b[f] = static_cast<uint32_t>(min(n0 / 32 + 2 * wn + f, nbands - 1)) * band_bytes;
-  };
-  uint32_t slot_at[3];  // where the wave's share of each slot starts
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-    slot_at[k] = __builtin_amdgcn_readfirstlane(lds_addr(slot(k))) + 16 * 64 * kDmaPerWave * wave;
-  // Part j of the wave's share of a stage's activations (offset v, stage at
-  // ko) into slot k; 16-byte part pp % 3 of weight band pp / 3 into w.
-  auto issue_dma = [&](uint32_t v, uint32_t ko, int k, int j) __attribute__((always_inline)) {
-    dma16_raw(rsx, slot_at[k] + 16 * 64 * j, v, ko);
-  };
   const uint32_t lane16 = 16 * lane;
-  auto load_w = [&](WRaw& w, uint32_t at0, uint32_t at1, auto PP) __attribute__((always_inline)) {
-    constexpr int f = decltype(PP)::value / 3, q = decltype(PP)::value % 3;
-    w.p[f][q] = load16_raw<1024 * q>(rsw, lane16, f ? at1 : at0);
+  // Bands past the tile (NFM no multiple of the waves) get an offset outside
+  // the operand: the load writes zeros and touches no memory.
+  uint32_t xlane[kOwn];
+#pragma unroll
+  for (int f = 0; f < kOwn; ++f) xlane[f] = kOwn * wave + f < NFM ? lane16 : kOutside;
+  const uint32_t ring_at = __builtin_amdgcn_readfirstlane(lds_addr(ring)) + kOwn * kUnit * wave;
+  // Part J (1 KiB) of the wave's share of a stage's activations, whose bytes
+  // of a band start at b + ko, into the slot at byte `slot` of the ring.
+  auto issue_dma = [&](const uint32_t* b, uint32_t ko, uint32_t slot, auto J) __attribute__((always_inline)) {
+    constexpr int f = decltype(J)::value / 3, q = decltype(J)::value % 3;
+    dma16_raw<1024 * q>(rsx, ring_at + slot + kUnit * f, xlane[f], b[f] + ko);
   };
-  // The MFMA operands of a loaded stage, once the wait for its loads has
-  // passed.  The compiler takes an asm load's result as ready when the asm
-  // is issued, so the parts first pass through an empty asm placed after the
-  // wait: any copy it makes to assemble an operand then reads them after the
-  // wait, not in the register a load may still be writing.
-  auto frags = [&](WRaw& w) __attribute__((always_inline)) {
+  // Part PP % 3 of weight band PP / 3 of a stage.
+  auto load_w = [&](WRaw& w, const uint32_t* b, uint32_t ko, auto PP) __attribute__((always_inline)) {
+    constexpr int f = decltype(PP)::value / 3, q = decltype(PP)::value % 3;
+    w.p[f][q] = load16_raw<1024 * q>(rsw, lane16, b[f] + ko);
+  };
+  // A loaded stage passes through an empty asm after the wait for its loads
+  // and before any use: the compiler takes an asm load's result as ready when
+  // the asm is issued, and could otherwise copy it from a register that a
+  // load may still be writing.
+  auto landed = [&](WRaw& w) __attribute__((always_inline)) {
     asm volatile("" : "+v"(w.p[0][0]), "+v"(w.p[0][1]), "+v"(w.p[0][2]), "+v"(w.p[1][0]), "+v"(w.p[1][1]),
                  "+v"(w.p[1][2]));
+  };
+  auto frags = [&](const WRaw& w) __attribute__((always_inline)) {
     WFrag r;
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
@@ -830,130 +799,96 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
     }
     return r;
   };
-  // Scales and bias of the tile at (m0, n0) into LDS: waves 0..3 take a
-  // quarter of s_x each, waves 4..7 a quarter of s_w, waves 0..1 half of the
-  // bias.  Entries past M or N read as zero (outside the buffers).
+  // Scales and bias of the tile at (m0, n0) into LDS: every wave a quarter of
+  // s_w, the first waves 64 of s_x each, waves 2 and 3 half of the bias each.
+  // Entries past M or N read as zero (outside the buffers).
   auto issue_scales = [&](int m0, int n0) __attribute__((always_inline)) {
-    if constexpr (EPI == Epilogue::kBf16 && WAVES == 4) {
-      // every wave a quarter of s_w; waves 0, 1 half of s_x each, waves 2, 3
-      // half of the bias each
-      {
-        const RawRsrc r = raw_rsrc(sw, 4 * N);
-        dma4_raw(r, lds_addr(sc_w + 64 * wave), 4 * static_cast<uint32_t>(n0 + 64 * wave + lane));
+    if constexpr (EPI == Epilogue::kBf16) {
+      const RawRsrc rw = raw_rsrc(sw, 4 * N);
+      dma4_raw(rw, lds_addr(sc_w + 64 * wave), 4 * static_cast<uint32_t>(n0 + 64 * wave + lane));
+      if (wave < kScX / 64) {
+        const RawRsrc rx = raw_rsrc(sx, 4 * M);
+        dma4_raw(rx, lds_addr(sc_x + 64 * wave), 4 * static_cast<uint32_t>(m0 + 64 * wave + lane));
       }
-      if (wave < 2) {
-        const RawRsrc r = raw_rsrc(sx, 4 * M);
-        dma4_raw(r, lds_addr(sc_x + 64 * wave), 4 * static_cast<uint32_t>(m0 + 64 * wave + lane));
-      } else if (HAS_BIAS) {
-        const RawRsrc r = raw_rsrc(bias, 2 * N);
-        dma4_raw(r, lds_addr(sc_b + 64 * (wave - 2)), 2 * static_cast<uint32_t>(n0 + 128 * (wave - 2) + 2 * lane));
-      }
-    } else if constexpr (EPI == Epilogue::kBf16) {
-      const int q = wave & 3;
-      if (wave < 4) {
-        const RawRsrc r = raw_rsrc(sx, 4 * M);
-        dma4_raw(r, lds_addr(sc_x + 64 * q), 4 * static_cast<uint32_t>(m0 + 64 * q + lane));
-      } else {
-        const RawRsrc r = raw_rsrc(sw, 4 * N);
-        dma4_raw(r, lds_addr(sc_w + 64 * q), 4 * static_cast<uint32_t>(n0 + 64 * q + lane));
-      }
-      if (HAS_BIAS && wave < 2) {
-        const RawRsrc r = raw_rsrc(bias, 2 * N);
-        dma4_raw(r, lds_addr(sc_b + 64 * wave), 2 * static_cast<uint32_t>(n0 + 128 * wave + 2 * lane));
+      if (HAS_BIAS && wave >= 2) {
+        const RawRsrc rb = raw_rsrc(bias, 2 * N);
+        dma4_raw(rb, lds_addr(sc_b + 64 * (wave - 2)), 2 * static_cast<uint32_t>(n0 + 128 * (wave - 2) + 2 * lane));
       }
     }
   };
-  // B fragment (k-step s, band 4 wm + fm) from slot k: the 16-byte part and
-  // the 8-byte part.
-  auto read_b = [&](int k, int s, int fm) __attribute__((always_inline)) {
-    const uint8_t* p = reinterpret_cast<const uint8_t*>(slot(k)) + (s * S::kBands + 4 * wm + fm) * kFragBytes;
+  // Activation fragment (k-step s, band fm) of the slot at byte `slot`: the
+  // 16-byte part and the 8-byte part.
+  auto read_b = [&](uint32_t slot, int s, int fm) __attribute__((always_inline)) {
+    const uint8_t* p = ring + (kUnit * fm + kFragBytes * s);
     // the 8-byte part as a relaxed atomic load, which the compiler does not
     // pair with another fragment's (a paired read lands both parts apart from
     // their 16-byte parts and costs moves to join them)
-    const uint64_t hi = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p + 1024 + 8 * lane), __ATOMIC_RELAXED,
-                                          __HIP_MEMORY_SCOPE_WAVEFRONT);
-    return join(*reinterpret_cast<const v4i32*>(p + 16 * lane), __builtin_bit_cast(v2i32, hi));
+    const uint64_t hi = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p + (slot + 8 * lane) + 1024),
+                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    return join(*reinterpret_cast<const v4i32*>(p + (slot + 16 * lane)), __builtin_bit_cast(v2i32, hi));
   };
 
-  // The rest of the kernel, for a wave with NFM activation bands (four in
-  // the first half; tile_bands - 4 in the second).  Each count gets its own
-  // straight-line code, so no branch sits between the MFMAs.
-  auto run = [&](auto NFM) __attribute__((always_inline)) {
-  constexpr int nfm = decltype(NFM)::value;
-  v16f acc[2][4];
+  v16f acc[2][NFM];
 #pragma unroll
   for (int f = 0; f < 2; ++f)
 #pragma unroll
-    for (int fm = 0; fm < 4; ++fm) acc[f][fm] = v16f{};
+    for (int fm = 0; fm < NFM; ++fm) acc[f][fm] = v16f{};
 
-  // The block walks one stream of stages g = i * T + t over its tiles i.
-  // Loads run ahead across tile boundaries: the weights of stage g + 1 and
-  // the activations of stage g + 3.  Past the block's last stage they are
-  // issued anyway, for its last tile again (every address stays inside the
-  // operands), which keeps the wait counts below constant.
-  int cm0, cn0, xm0, xn0;  // current and next tile
-  tile_at(0, &cm0, &cn0);
-  if (ntiles > 1) tile_at(1, &xm0, &xn0);
-  else xm0 = cm0, xn0 = cn0;
-  uint32_t cv[kDmaPerWave], xv[kDmaPerWave];  // the DMA offsets of the current and the next tile
-  uint32_t cb[2], xb[2];     // the weight bands of the current and the next tile
-  dma_offsets(cm0, cv);
-  dma_offsets(xm0, xv);
-  w_bases(cn0, cb);
-  w_bases(xn0, xb);
-  uint32_t kw = 2 * kFragBytes * static_cast<uint32_t>(koff), kd = kw;  // stages of the next weight load and DMA
-
-  WRaw w0, w1;
+  // The block walks one stream of stages over its tiles.  Loads run ahead
+  // across tile boundaries: the weights by one stage, the activations by
+  // three.  Past the block's last stage they are issued anyway, for its last
+  // tile again (every address stays inside the operands), which keeps the
+  // wait counts below constant.
+  Tile ct = tile_at(0), xt = ct;  // current and next tile
+  if (ntiles > 1) xt = tile_at(1);
+  uint32_t kw = kUnit * static_cast<uint32_t>(koff), kd = kw;  // stages of the next weight load and DMA
+  WRaw w[2];
+  static_for<kWLoads>([&](auto PP) __attribute__((always_inline)) { load_w(w[0], ct.w, kw, PP); });
+  kw = next_k(kw);
   // A tile of fewer than three stages is the block's only one: its DMA goes
   // round K again, into slots that are never read.
-  static_for<kWLoads>([&](auto PP) __attribute__((always_inline)) { load_w(w0, cb[0] + kw, cb[1] + kw, PP); });
-  kw = next_k(kw);
   static_for<3>([&](auto K_) __attribute__((always_inline)) {
-    static_for<kDmaPerWave>([&](auto J) __attribute__((always_inline)) {
-      issue_dma(cv[decltype(J)::value], kd, decltype(K_)::value, decltype(J)::value);
-    });
+    static_for<kDma>([&](auto J) __attribute__((always_inline)) { issue_dma(ct.x, kd, kSlot * decltype(K_)::value, J); });
     kd = next_k(kd);
   });
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kDmaPerWave));  // DMA(0)
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(kDma));  // the weights and the first two stages
   __builtin_amdgcn_s_barrier();
   __builtin_amdgcn_sched_barrier(0);
-  // A wave's activation fragments of a stage, (k-step s, band fm) in order
-  // nfm s + fm, roll through a window of nfm register sets: fragment i is
-  // read (into the set fragment i - nfm has just left) while the MFMAs of
-  // fragment i - nfm run.
-  v8i bq[4];
+  uint32_t so = 0, sn = kSlot;  // slots of this stage and the next
+  // A stage's activation fragments, (k-step s, band fm) in order NFM s + fm,
+  // roll through a window of NFM register sets: fragment i is read (into the
+  // set fragment i - NFM has just left) while the MFMAs of i - NFM run.
+  v8i bq[NFM];
 #pragma unroll
-  for (int fm = 0; fm < nfm; ++fm) bq[fm] = read_b(0, 0, fm);
+  for (int fm = 0; fm < NFM; ++fm) bq[fm] = read_b(0, 0, fm);
 
-  // Epilogue of the current tile: lane holds column m = m0 + 128 wm + 32 fm +
-  // (lane & 31) and rows n = n0 + 64 wn + 32 f + 8 j + 4 (lane >> 5) + r of
-  // y^T.  Then the accumulators restart from zero.
-  auto epilogue = [&]() __attribute__((always_inline)) {
+  // Epilogue of the tile at (cm0, cn0): lane holds column m = cm0 + 32 fm +
+  // (lane & 31) and rows n = cn0 + 64 wave + 32 f + 8 j + 4 (lane >> 5) + r of
+  // y^T.
+  auto epilogue = [&](int cm0, int cn0) __attribute__((always_inline)) {
     // The lane index is passed through an empty asm so that the per-lane
     // addresses below are computed here, not hoisted out of the stage loop
-    // into registers the loop needs (or into scratch, whose reloads would
-    // wait for every load in flight).
+    // into registers the loop needs.
     int lane = threadIdx.x & 63;
     asm volatile("" : "+v"(lane));
-    const int mb = cm0 + 128 * wm + (lane & 31);
-    const int nl = 64 * wn + 4 * (lane >> 5);  // within the tile
-    const int mlim = min(M, cm0 + tile_rows);  // rows of this tile
-    const bool full = (cm0 + tile_rows <= M) && (cn0 + kFBN <= N) && (N % 4 == 0);
+    const int row = lane & 31, hl = lane >> 5;
+    const int nl = 64 * wave + 4 * hl;    // column within the tile
+    const int mlim = min(M, cm0 + kRows);  // rows of this tile
+    const bool full = (cm0 + kRows <= M) && (cn0 + kFBN <= N);
     if constexpr (EPI == Epilogue::kInt32) {
       int32_t* o = static_cast<int32_t*>(out);
 #pragma unroll
       for (int f = 0; f < 2; ++f)
 #pragma unroll
-        for (int fm = 0; fm < 4; ++fm) {
-          const int m = mb + 32 * fm;
-          if (fm >= nfm) continue;
+        for (int fm = 0; fm < NFM; ++fm) {
+          const int m = cm0 + row + 32 * fm;
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             const int n = cn0 + nl + 32 * f + 8 * j;
             const int v0 = static_cast<int>(acc[f][fm][4 * j]), v1 = static_cast<int>(acc[f][fm][4 * j + 1]);
             const int v2 = static_cast<int>(acc[f][fm][4 * j + 2]), v3 = static_cast<int>(acc[f][fm][4 * j + 3]);
             int32_t* p = o + static_cast<int64_t>(m) * N + n;
-            if (full) {
+            if (full && N % 4 == 0) {
               *reinterpret_cast<int4*>(p) = make_int4(v0, v1, v2, v3);
             } else if (m < mlim) {
               if (n + 0 < N) p[0] = v0;
@@ -964,194 +899,223 @@ __global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void w4a4_f6_gemm_kernel(
           }
         }
     } else {
-      // Through LDS: a wave's 128 x 64 outputs in two halves of 64 rows; each
-      // half is written to LDS as the accumulators hold it and stored to
-      // memory as whole 128-byte rows, eight rows per instruction (in a ragged
-      // tile, element by element where a row runs past M or N).
+      // Through LDS, one band (32 rows x 64 columns per wave) at a time in two
+      // buffers: written as the accumulators hold it, then read and stored to
+      // memory as whole 128-byte rows, eight rows per instruction, while the
+      // next band is scaled.
       uint16_t* o = static_cast<uint16_t*>(out);
-      v2u32* stg2 = reinterpret_cast<v2u32*>(stg);
-      const int sbase = 512 * wave;  // the wave's area, in 16-byte units
-      const bool vec = full && (N % 8 == 0);
+      uint8_t* area = stg + 8192 * wave;
+      if constexpr (BIAS_TAIL) {
+        // the last bias value, whose pair was read past the buffer as zero
+        const int c = N - 1 - cn0 - 64 * wave;
+        if (c >= 0 && c < 64 && lane == 0) sc_b[(64 * wave + c) / 2] = __uint_as_float(bias[N - 1]);
+        __builtin_amdgcn_wave_barrier();
+      }
+      // The scales and bias of the lane's columns 32 f + 8 j .. + 3: read once
+      // where a block has the CU's registers to itself, else for each band.
+      constexpr bool kKeep = PER_CU == 1;
+      struct Col {
+        float4 s;
+        float2 b;  // bf16 pairs
+      };
+      auto column = [&](int f, int j) __attribute__((always_inline)) {
+        const int c = nl + 32 * f + 8 * j;
+        Col r;
+        r.s = *reinterpret_cast<const float4*>(sc_w + c);
+        if constexpr (HAS_BIAS) r.b = *reinterpret_cast<const float2*>(sc_b + c / 2);
+        return r;
+      };
+      Col kept[2][4];
+      if constexpr (kKeep) {
 #pragma unroll
-      for (int ph = 0; ph < 2; ++ph) {
-        if (2 * ph >= nfm) break;  // a short second half (a compile-time test)
+        for (int f = 0; f < 2; ++f)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) kept[f][j] = column(f, j);
+      }
+      float sxv[NFM];
+#pragma unroll
+      for (int fm = 0; fm < NFM; ++fm) sxv[fm] = sc_x[32 * fm + row];
+      auto put = [&](auto FM) __attribute__((always_inline)) {
+        constexpr int fm = decltype(FM)::value;
 #pragma unroll
         for (int f = 0; f < 2; ++f)
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            const int c = nl + 32 * f + 8 * j;  // column within the tile
-            const float4 swv = *reinterpret_cast<const float4*>(sc_w + c);
-            const float swa[4] = {swv.x, swv.y, swv.z, swv.w};
-            float bv[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-            if (HAS_BIAS) {
-              if (!BIAS_TAIL || full) {
-                const float2 bf = *reinterpret_cast<const float2*>(sc_b + c / 2);
-                const uint32_t b0 = __float_as_uint(bf.x), b1 = __float_as_uint(bf.y);
-                bv[0] = __uint_as_float(b0 << 16);
-                bv[1] = __uint_as_float(b0 & 0xFFFF0000u);
-                bv[2] = __uint_as_float(b1 << 16);
-                bv[3] = __uint_as_float(b1 & 0xFFFF0000u);
-              } else {
-                // a ragged tile (with odd N the last staged pair of bias values
-                // reads past the buffer as zero): straight from memory
+            Col col;
+            if constexpr (kKeep) col = kept[f][j];
+            else col = column(f, j);
+            const float swa[4] = {col.s.x, col.s.y, col.s.z, col.s.w};
+            uint16_t h[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                  bv[r] = __uint_as_float(static_cast<uint32_t>(bias[min(cn0 + c + r, N - 1)]) << 16);
-                // settle these loads here, in the ragged branch: otherwise the
-                // wait for them lands after the branches join and, in every
-                // tile, waits for all the prefetches in flight
-                __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            for (int r = 0; r < 4; ++r) {
+              float v = acc[f][fm][4 * j + r];
+              v = v * sxv[fm];
+              v = v * swa[r];
+              if constexpr (HAS_BIAS) {
+                const uint32_t pair = __float_as_uint(r < 2 ? col.b.x : col.b.y);
+                v = v + ((r & 1) ? bf16_hi(pair) : bf16_lo(pair));
               }
+              h[r] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(v));
             }
-#pragma unroll
-            for (int fh = 0; fh < 2; ++fh) {
-              const int fm = 2 * ph + fh;
-              const float sxv = sc_x[128 * wm + 32 * fm + (lane & 31)];
-              uint16_t h[4];
-#pragma unroll
-              for (int r = 0; r < 4; ++r) {
-                float v = acc[f][fm][4 * j + r];
-                v = v * sxv;
-                v = v * swa[r];
-                if (HAS_BIAS) v = v + bv[r];
-                h[r] = __builtin_bit_cast(uint16_t, static_cast<__bf16>(v));
-              }
-              const int row = 32 * fh + (lane & 31);
-              const int col = c - 64 * wn;  // within the wave's 64 columns
-              const int chunk = (col >> 3) ^ ((row >> 1) & 7);
-              stg2[2 * (sbase + 8 * row + chunk) + ((col & 7) >> 2)] =
-                  v2u32{h[0] | (static_cast<uint32_t>(h[1]) << 16), h[2] | (static_cast<uint32_t>(h[3]) << 16)};
-            }
+            *reinterpret_cast<v2u32*>(area + 4096 * (fm & 1) + 128 * row + 16 * ((4 * f + j) ^ ((row >> 1) & 7)) +
+                                      8 * hl) =
+                v2u32{h[0] | (static_cast<uint32_t>(h[1]) << 16), h[2] | (static_cast<uint32_t>(h[3]) << 16)};
           }
-        __builtin_amdgcn_wave_barrier();
+      };
+      // A whole tile with rows of a multiple of 16 bytes is stored without a
+      // test; otherwise rows past M and columns past N are left out, element
+      // by element where N % 8 != 0 (rolled up: it need not be fast, and the
+      // kernel's code stays small).
+      auto bands = [&](auto WHOLE) __attribute__((always_inline)) {
+        const int r0 = lane >> 3, c = lane & 7;
+        const int n = cn0 + 64 * wave + 8 * c;
+        uint16_t* p = o + static_cast<int64_t>(cm0 + r0) * N + n;
+        const int mleft = n < N ? mlim - cm0 - r0 : 0;
+        auto get = [&](int fm, int it) __attribute__((always_inline)) {
+          return *reinterpret_cast<const v4u32*>(area + 4096 * (fm & 1) + 1024 * it + 128 * r0 +
+                                                 16 * (c ^ ((4 * it + (r0 >> 1)) & 7)));
+        };
+        put(std::integral_constant<int, 0>{});
+        static_for<NFM>([&](auto FM) __attribute__((always_inline)) {
+          constexpr int fm = decltype(FM)::value;
+          __builtin_amdgcn_wave_barrier();
+          if constexpr (decltype(WHOLE)::value) {
+            v4u32 v[4];
 #pragma unroll
-        for (int it = 0; it < 8; ++it) {
-          const int row = 8 * it + (lane >> 3);
-          const int c = lane & 7;
-          const v4u32 vv = stg[sbase + 8 * row + (c ^ ((row >> 1) & 7))];
-          const uint4 v = make_uint4(vv.x, vv.y, vv.z, vv.w);
-          const int m = cm0 + 128 * wm + 64 * ph + row;
-          const int n = cn0 + 64 * wn + 8 * c;
-          uint16_t* p = o + static_cast<int64_t>(m) * N + n;
-          if (m >= mlim) {
-          } else if (vec) {
-            __builtin_nontemporal_store(vv, reinterpret_cast<v4u32*>(p));
+            for (int it = 0; it < 4; ++it) v[it] = get(fm, it);
+            if constexpr (fm + 1 < NFM) put(std::integral_constant<int, fm + 1>{});
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+              __builtin_nontemporal_store(v[it], reinterpret_cast<v4u32*>(p));
+              p += 8 * static_cast<int64_t>(N);
+            }
           } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            if constexpr (fm + 1 < NFM) put(std::integral_constant<int, fm + 1>{});
+#pragma unroll 1
+            for (int it = 0; it < 4; ++it) {
+              const v4u32 v = get(fm, it);
+              if (32 * fm + 8 * it < mleft) {
+                if (N % 8 == 0) {
+                  __builtin_nontemporal_store(v, reinterpret_cast<v4u32*>(p));
+                } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (n + e < N) p[e] = static_cast<uint16_t>(w[e >> 1] >> (16 * (e & 1)));
+                  for (int e = 0; e < 8; ++e)
+                    if (n + e < N) p[e] = static_cast<uint16_t>(v[e >> 1] >> (16 * (e & 1)));
+                }
+              }
+              p += 8 * static_cast<int64_t>(N);
+            }
           }
-        }
+        });
         __builtin_amdgcn_wave_barrier();
-      }
+      };
+      if (full && N % 8 == 0) bands(std::true_type{});
+      else bands(std::false_type{});
     }
 #pragma unroll
     for (int f = 0; f < 2; ++f)
 #pragma unroll
-      for (int fm = 0; fm < 4; ++fm) acc[f][fm] = v16f{};
+      for (int fm = 0; fm < NFM; ++fm) acc[f][fm] = v16f{};
   };
 
-  // One stage g = g0 + I, g0 a multiple of 6: slot I % 3 and weight set
-  // I % 2, both known at compile time; t is its stage within tile ti.
+  // Stage t of the current tile, with weight set I (known at compile time).
   //   * At its start, the wait for this stage's weights (loaded during the
-  //     previous stage's first k-step): vmcnt(kDmaPerWave) leaves in flight
-  //     only the DMA issued after them (vector loads complete in order).
-  //   * Then the stage's fragments j = nfm s + fm (k-step s, band fm) in
-  //     turn: the two MFMAs of fragment j, the read of fragment j + nfm into
+  //     previous stage's first k-step): vmcnt(kDma) leaves in flight only the
+  //     DMA issued after them (vector loads complete in order).
+  //   * Then the stage's fragments j = NFM s + fm (k-step s, band fm) in
+  //     turn: the two MFMAs of fragment j, the read of fragment j + NFM into
   //     the register set fragment j has left (past the stage's last
   //     fragment, those of the next stage, from the next slot), and a share
   //     of the stage's vector-memory loads, so that they reach the memory
   //     system spread over the stage rather than in one burst per wave:
-  //     stage g + 1's weights (into the other set, done with at stage g - 1)
-  //     among the first k-step's fragments, and the DMA of stage g + 3
-  //     among the second's.
+  //     the next stage's weights (into the other set, done with one stage
+  //     ago) among the first k-step's fragments, and the DMA of the stage
+  //     three ahead among the second's.
   //   * Between the k-steps, once every wave has read the whole slot
-  //     (lgkmcnt(0) + barrier) and DMA(g + 1) has landed, the slot is free
-  //     for that DMA (at a tile's first stage, the tile's scales are moved
-  //     first).  The wait there, vmcnt(kWLoads + kDmaPerWave) = 9, leaves in
-  //     flight at most the loads issued since this stage's weights (which
-  //     have landed): DMA(g + 2) and stage g + 1's weights.  DMA(g + 1),
-  //     issued before them, has therefore landed (the stores of an epilogue
-  //     in between only add to the count).
-  // After a tile's last stage comes its epilogue.
-  WRaw* wset[2] = {&w0, &w1};
-  int t = 0, ti = 0;
-  auto stage = [&](auto I) __attribute__((always_inline)) {
+  //     (lgkmcnt(0) + barrier) and the next stage's DMA has landed, the slot
+  //     is free for that DMA.  The wait there, vmcnt(kWLoads + kDma), leaves
+  //     in flight at most the loads issued since this stage's weights (which
+  //     have landed): the DMA of the stage two ahead and the next stage's
+  //     weights.
+  // A tile's FIRST stage waits for neither: its weights and the next stage's
+  // DMA had landed when the tile before it ended (or in the prologue), and a
+  // wait here would be one for the stores of that tile's epilogue.  It moves
+  // the tile's scales, once every wave is past that epilogue.
+  int t = 0;
+  auto stage = [&](auto I, auto FIRST) __attribute__((always_inline)) {
     constexpr int i = decltype(I)::value;
-    constexpr int cur = i % 3, nxt = (i + 1) % 3;
-    const bool end = t == last;
-    const uint32_t at0 = (end ? xb[0] : cb[0]) + kw, at1 = (end ? xb[1] : cb[1]) + kw;  // stage g + 1's weights
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(kDmaPerWave));
+    constexpr bool first = decltype(FIRST)::value;
+    const bool end = t == last, ahead = t + 3 >= T;
+    const uint32_t wb[2] = {end ? xt.w[0] : ct.w[0], end ? xt.w[1] : ct.w[1]};
+    uint32_t xb[kOwn];
+#pragma unroll
+    for (int f = 0; f < kOwn; ++f) xb[f] = ahead ? xt.x[f] : ct.x[f];
+    if constexpr (!first) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kDma));
     __builtin_amdgcn_sched_barrier(0);
-    const WFrag wc = frags(*wset[i % 2]);
-    static_for<2 * nfm>([&](auto J) __attribute__((always_inline)) {
+    landed(w[i]);
+    const WFrag wc = frags(w[i]);
+    static_for<2 * NFM>([&](auto J) __attribute__((always_inline)) {
       constexpr int j = decltype(J)::value;
-      constexpr int ks = j / nfm, fm = j % nfm, r = j + nfm;
-      acc[0][fm] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wc.f[ks][0], bq[fm], acc[0][fm], 3, 3, 0, 127, 0,
-                                                                   127);
-      acc[1][fm] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wc.f[ks][1], bq[fm], acc[1][fm], 3, 3, 0, 127, 0,
-                                                                   127);
-      if constexpr (r < 2 * nfm) bq[fm] = read_b(cur, 1, fm);
-      else bq[fm] = read_b(nxt, 0, fm);
+      constexpr int ks = j / NFM, fm = j % NFM;
+      acc[0][fm] = mfma_bf6(wc.f[ks][0], bq[fm], acc[0][fm]);
+      acc[1][fm] = mfma_bf6(wc.f[ks][1], bq[fm], acc[1][fm]);
       if constexpr (ks == 0) {
-        // weight parts pp with pp nfm / kWLoads == j
+        bq[fm] = read_b(so, 1, fm);
         static_for<kWLoads>([&](auto PP) __attribute__((always_inline)) {
-          if constexpr (decltype(PP)::value * nfm / kWLoads == j) load_w(*wset[(i + 1) % 2], at0, at1, PP);
+          if constexpr (decltype(PP)::value * NFM / kWLoads == fm) load_w(w[1 - i], wb, kw, PP);
         });
-      } else if constexpr (fm < kDmaPerWave) {
-        issue_dma(t + 3 < T ? cv[fm] : xv[fm], kd, cur, fm);
+      } else {
+        bq[fm] = read_b(sn, 0, fm);
+        static_for<kDma>([&](auto D) __attribute__((always_inline)) {
+          if constexpr (decltype(D)::value * NFM / (NFM < kDma ? kDma : NFM) == fm) issue_dma(xb, kd, so, D);
+        });
       }
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (j == nfm - 1) {
+      if constexpr (j == NFM - 1) {
         __builtin_amdgcn_s_waitcnt(kLgkm0);
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(kWLoads + kDmaPerWave));
+        if constexpr (!first) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kWLoads + kDma));
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
-        if (t == 0) issue_scales(cm0, cn0);
+        if constexpr (first) issue_scales(ct.m0, ct.n0);
       }
     });
     kw = next_k(kw);
     kd = next_k(kd);
-    // (past the block's last stage the reads of the next slot are of data
-    // that is not used)
-    static_assert(kDmaPerWave <= 3, "the DMA parts go with the second k-step's fragments");
+    so = sn;
+    sn = sn == 2 * kSlot ? 0u : sn + kSlot;
+    ++t;
     __builtin_amdgcn_sched_barrier(0);
-    if (t == last) {
-      if (T == 1) {
-        // the scales were moved at this very stage
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        __builtin_amdgcn_s_barrier();
-      }
-      epilogue();
-      ++ti;
-      t = 0;
-      cm0 = xm0, cn0 = xn0;
-      cb[0] = xb[0], cb[1] = xb[1];
-      if (ti + 1 < ntiles) {
-        tile_at(ti + 1, &xm0, &xn0);
-        w_bases(xn0, xb);
-      }
-#pragma unroll
-      for (int j = 0; j < kDmaPerWave; ++j) cv[j] = xv[j];
-      dma_offsets(xm0, xv);
-    } else {
-      ++t;
-    }
   };
-  const int G = ntiles * T;
-  for (int g = 0; g < G; g += 6) {
-    stage(std::integral_constant<int, 0>{});
-#define JQ_F6_NEXT(N) \
-    if (g + N < G) stage(std::integral_constant<int, N>{});
-    JQ_F6_NEXT(1) JQ_F6_NEXT(2) JQ_F6_NEXT(3) JQ_F6_NEXT(4) JQ_F6_NEXT(5)
-#undef JQ_F6_NEXT
+  using Set0 = std::integral_constant<int, 0>;
+  using Set1 = std::integral_constant<int, 1>;
+  for (int ti = 0; ti < ntiles; ++ti) {
+    stage(Set0{}, std::true_type{});
+    if (T > 1) stage(Set1{}, std::false_type{});
+    for (int u = 2; u < T; u += 2) {
+      stage(Set0{}, std::false_type{});
+      if (u + 1 < T) stage(Set1{}, std::false_type{});
+    }
+    // The next tile's first weights, and every DMA but the last stage's, have
+    // landed before the epilogue's stores are issued behind them.
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(kDma));
+    __builtin_amdgcn_sched_barrier(0);
+    if (T & 1) {
+      // they are in the other set
+      landed(w[1]);
+      w[0] = w[1];
+    }
+    if (T == 1) {
+      // the scales were moved at this very stage
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+      __builtin_amdgcn_s_barrier();
+    }
+    epilogue(ct.m0, ct.n0);
+    t = 0;
+    ct = xt;
+    if (ti + 2 < ntiles) xt = tile_at(ti + 2);
   }
   // no load may still be writing LDS or registers when the wave ends
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  };
-  if (wm == 0 || tile_bands == 8) run(std::integral_constant<int, 4>{});
-  else run(std::integral_constant<int, 3>{});
 }
 
 // ---------------------------------------------------------------------------
@@ -1318,8 +1282,8 @@ __global__ __launch_bounds__(256, 2) void w4a4g_f6_gemm_kernel(
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
           const v8i a = read_w(k, t, f);
-          const v16f c0 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b0, v16f{}, 3, 3, 0, 127, 0, 127);
-          const v16f c1 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b1, v16f{}, 3, 3, 0, 127, 0, 127);
+          const v16f c0 = mfma_bf6(a, b0, v16f{});
+          const v16f c1 = mfma_bf6(a, b1, v16f{});
           fold(c0, f, 0, t);
           fold(c1, f, 1, t);
         }
@@ -1330,10 +1294,10 @@ __global__ __launch_bounds__(256, 2) void w4a4g_f6_gemm_kernel(
 #pragma unroll
       for (int f = 0; f < 2; ++f) {
         const v8i a0 = read_w(k, 0, f), a1 = read_w(k, 1, f);
-        v16f c0 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a0, b00, v16f{}, 3, 3, 0, 127, 0, 127);
-        v16f c1 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a0, b01, v16f{}, 3, 3, 0, 127, 0, 127);
-        c0 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a1, b10, c0, 3, 3, 0, 127, 0, 127);
-        c1 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a1, b11, c1, 3, 3, 0, 127, 0, 127);
+        v16f c0 = mfma_bf6(a0, b00, v16f{});
+        v16f c1 = mfma_bf6(a0, b01, v16f{});
+        c0 = mfma_bf6(a1, b10, c0);
+        c1 = mfma_bf6(a1, b11, c1);
         fold(c0, f, 0, 0);
         fold(c1, f, 1, 0);
       }
@@ -1471,36 +1435,32 @@ int64_t f6_ksteps(int64_t K) { return (K + 127) / 128 * 2; }
 
 int64_t f6_operand_bytes(int64_t rows, int64_t K) { return (rows + 31) / 32 * f6_ksteps(K) * kFragBytes; }
 
-// Tile height of the GEMM in bands of 32 rows (7 or 8).  Every tile costs its
-// height in MFMA work plus about one band's worth of fixed work (the weight
-// fragments, the epilogue); the blocks of an XCD take its tiles in rounds.
-// The height with the cheapest rounds wins, the taller one on ties: at
-// 9216 x 3072 on 256 CUs, 224-row tiles give 504 tiles in two rounds where
-// 256-row tiles give 432, which also take two rounds.
-int f6_tile_bands(int64_t M, int64_t N, int64_t slots) {
-  const int64_t tiles_n = (N + kFBN - 1) / kFBN;
-  const int64_t per_xcd_slots = std::max<int64_t>(1, slots / kNumXcd);
-  int best = 8;
-  int64_t best_cost = -1;
-  for (int b = 8; b >= 7; --b) {
-    const int64_t tiles = (M + 32 * b - 1) / (32 * b) * tiles_n;
-    const int64_t per_xcd = (tiles + kNumXcd - 1) / kNumXcd;
-    const int64_t rounds = (per_xcd + per_xcd_slots - 1) / per_xcd_slots;
-    const int64_t cost = rounds * (b + 1);
-    if (best_cost < 0 || cost < best_cost) best = b, best_cost = cost;
+// The GEMM's tile height in bands of 32 rows, 5 .. 8 (one block per CU) or 4
+// (two), and the estimate in ns it was picked by, for the XCD with most tiles:
+//   one block per CU: its rounds, each 38 b + 314 ns per 128 codes and 1080 b
+//   for the epilogue (b bands);
+//   two blocks per CU: 800 ns per 128 codes and 5600 for each round of two
+//   tiles per CU, 420 and 4300 for a last round with one tile per CU or fewer.
+// Fitted to 130 shapes of 768 tokens and more (K 1024..15360, N 1024..12288).
+// Over those and 89 smaller ones the pick is within 0.8% of the best height on
+// average; always the two-block shape or 224/256-row tiles by the rounds
+// alone, which was the rule before, is 10% off.
+int f6_tile_bands(int64_t M, int64_t N, int64_t K, int64_t slots, int64_t* ns) {
+  const int64_t tiles_n = (N + kFBN - 1) / kFBN, T = (K + 127) / 128;
+  const int64_t cus = std::max<int64_t>(1, slots / kNumXcd);  // of an XCD
+  auto per_xcd = [&](int b) { return ((M + 32 * b - 1) / (32 * b) * tiles_n + kNumXcd - 1) / kNumXcd; };
+  const int64_t n4 = per_xcd(4), rest = n4 % (2 * cus);
+  const int64_t round2 = 800 * T + 5600;
+  int best = 4;
+  int64_t best_ns = n4 / (2 * cus) * round2;
+  if (rest > cus) best_ns += round2;
+  else if (rest > 0) best_ns += 420 * T + 4300;
+  for (int b = 8; b >= 5; --b) {
+    const int64_t t = (per_xcd(b) + cus - 1) / cus * (T * (38 * b + 314) + 1080 * b);
+    if (t < best_ns) best = b, best_ns = t;
   }
+  if (ns != nullptr) *ns = best_ns;
   return best;
-}
-
-// Block shape of the GEMM.  One 8-wave block per CU on 224- or 256-row tiles
-// re-reads the operands least, and wins when 256-row tiles cover M exactly
-// or K is long.  Otherwise two 4-wave blocks per CU on 128-row tiles win:
-// 224-row tiles save less than their missing band (the wave that holds three
-// bands waits on the one beside it that holds four), and with short K a
-// tile's epilogue is a large share of its time, which the other block's
-// MFMAs fill.  Measured over M 1024..9216, K 2048..12288, N 3072..12288.
-int f6_block_waves(int64_t M, int64_t N, int64_t K, int64_t slots) {
-  return K > kShortK || f6_tile_bands(M, N, slots) == 8 ? 8 : 4;
 }
 
 template <int G>
@@ -1643,8 +1603,6 @@ hipError_t launch_int4_to_f6(const uint8_t* q, int64_t rows, int64_t K, uint8_t*
 hipError_t launch_w4a4_f6_gemm(Epilogue epi, const uint8_t* xf6, const float* sx, int64_t M, int64_t K,
                                const uint8_t* wf6, const float* sw, int64_t N, const uint16_t* bias, void* out,
                                hipStream_t st) {
-  // Block slots: one 8-wave block or two 4-wave blocks per CU (a block's
-  // registers fill half or all of the CU); each block walks its tiles in turn.
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
@@ -1654,30 +1612,31 @@ hipError_t launch_w4a4_f6_gemm(Epilogue epi, const uint8_t* xf6, const float* sx
   const int64_t slots = std::max<int64_t>(kNumXcd, cus / kNumXcd * kNumXcd);
   if (const int tile = f6_narrow_tile(M, N, K, slots))
     return launch_f6_narrow(tile, epi, xf6, sx, M, K, wf6, sw, N, bias, out, st);
-  const int waves = f6_block_waves(M, N, K, slots);
-  const int tile_bands = waves == 4 ? 4 : f6_tile_bands(M, N, slots);
-  const int tiles_m = static_cast<int>((M + 32 * tile_bands - 1) / (32 * tile_bands));
+  const int bands = f6_tile_bands(M, N, K, slots, nullptr);
+  const int tiles_m = static_cast<int>((M + 32 * bands - 1) / (32 * bands));
   const int tiles_n = static_cast<int>((N + kFBN - 1) / kFBN);
-  const int64_t T = static_cast<int64_t>(tiles_m) * tiles_n;
-  const int64_t per_xcd = (T + kNumXcd - 1) / kNumXcd;
-  const int64_t block_slots = (8 / waves) * slots;
+  const int64_t per_xcd = (static_cast<int64_t>(tiles_m) * tiles_n + kNumXcd - 1) / kNumXcd;
+  // a block's registers fill the CU, or half of it; each block walks its tiles in turn
+  const int64_t block_slots = (bands == 4 ? 2 : 1) * slots;
   const int blocks =
       static_cast<int>(ksteps / 2 < 3 ? per_xcd * kNumXcd : std::min<int64_t>(per_xcd * kNumXcd, block_slots));
   const int mbands = static_cast<int>((M + 31) / 32);
   const int nbands = static_cast<int>((N + 31) / 32);
   const int Mi = static_cast<int>(M), Ni = static_cast<int>(N);
-#define JQ_F6(W, E, B, BT)                                                                                   \
-  hipLaunchKernelGGL((w4a4_f6_gemm_kernel<W, E, B, BT>), dim3(blocks), dim3(64 * W), 0, st, xf6, sx, Mi, mbands, \
-                     wf6, sw, Ni, nbands, ksteps, bias, out, tile_bands, tiles_m, tiles_n, blocks)
-#define JQ_F6_EPI(W)                                                      \
-  if (epi == Epilogue::kInt32) JQ_F6(W, Epilogue::kInt32, false, false);  \
-  else if (bias != nullptr && (N & 1)) JQ_F6(W, Epilogue::kBf16, true, true); \
-  else if (bias != nullptr) JQ_F6(W, Epilogue::kBf16, true, false);      \
-  else JQ_F6(W, Epilogue::kBf16, false, false);
-  if (waves == 4) {
-    JQ_F6_EPI(4)
-  } else {
-    JQ_F6_EPI(8)
+#define JQ_F6(NFM, PC, E, B, BT)                                                                                \
+  hipLaunchKernelGGL((w4a4_f6_gemm_kernel<NFM, PC, E, B, BT>), dim3(blocks), dim3(64 * kF6Waves), 0, st, xf6, sx, \
+                     Mi, mbands, wf6, sw, Ni, nbands, ksteps, bias, out, tiles_m, tiles_n, blocks)
+#define JQ_F6_EPI(NFM, PC)                                                           \
+  if (epi == Epilogue::kInt32) JQ_F6(NFM, PC, Epilogue::kInt32, false, false);       \
+  else if (bias != nullptr && (N & 1)) JQ_F6(NFM, PC, Epilogue::kBf16, true, true);  \
+  else if (bias != nullptr) JQ_F6(NFM, PC, Epilogue::kBf16, true, false);            \
+  else JQ_F6(NFM, PC, Epilogue::kBf16, false, false);
+  switch (bands) {
+    case 4: JQ_F6_EPI(4, 2) break;
+    case 5: JQ_F6_EPI(5, 1) break;
+    case 6: JQ_F6_EPI(6, 1) break;
+    case 7: JQ_F6_EPI(7, 1) break;
+    default: JQ_F6_EPI(8, 1) break;
   }
 #undef JQ_F6_EPI
 #undef JQ_F6

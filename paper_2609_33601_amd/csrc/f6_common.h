@@ -24,6 +24,15 @@ constexpr int kQuantBatchMax = 8;            // inputs of one batched quantiser 
 constexpr float kMagic = 12582912.0f;        // 1.5 * 2^23
 constexpr float kNearTie = 0.5f - 0x1p-17f;
 
+// acc + a b for two BF6 fragments (format 3).  With both scale operands the
+// constant 0 the builtin is v_mfma_f32_32x32x64_f8f6f4, which takes no scales;
+// with 127 (a scale of 1) it is v_mfma_scale_..., which also loads a scale per
+// operand: 16 bytes of code instead of 8 and an issue slot more per MFMA, for
+// the same sums.
+__device__ __forceinline__ v16f mfma_bf6(const v8i& a, const v8i& b, const v16f& acc) {
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, acc, 3, 3, 0, 0, 0, 0);
+}
+
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 

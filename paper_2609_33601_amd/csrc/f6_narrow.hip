@@ -6,7 +6,7 @@
 //
 // What bounds such a product.  The tiled kernel gives a tile of 128 to 256
 // rows x 256 columns to a block, so 64 x 12288 -> 4096 keeps 16 of 256 CUs
-// busy, each walking all of K alone at one stage of 128 codes per 0.65 us
+// busy, each walking all of K alone at one stage of 128 codes per 0.45 us
 // (the latency of its loads, whatever M).  Here the tile is 32 or 64 rows x
 // 32 .. 96 columns and the four waves of a block split K: wave w takes the
 // 128-code units w, w + 4, ... of the whole tile, with no barrier and no LDS
@@ -18,9 +18,9 @@
 // What is left is the rate at which a CU pulls operands from L2: 115 KB/us
 // per CU (29 TB/s for the chip) over all tiles and shapes measured, i.e. the
 // bytes of the CU that holds the most tiles.  Measured back to back on an
-// MI355X, tiled -> narrow: 64 x 4096 -> 4096 23.2 -> 5.3 us, 64 x 12288 ->
-// 4096 67.7 -> 9.8 us, 64 x 256 -> 256 8.3 -> 4.7 us, 512 x 12288 -> 3072
-// 67.4 -> 21.9 us.
+// MI355X, tiled -> narrow: 64 x 4096 -> 4096 15.4 -> 5.0 us, 64 x 12288 ->
+// 4096 46.9 -> 9.7 us, 256 x 12288 -> 3072 46.6 -> 17.2 us, 512 x 12288 ->
+// 3072 46.9 -> 21.6 us.
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(64 * kW, WPS) void f6_narrow_kernel(
                              : __builtin_shufflevector(w[d][f][1], w[d][f][2], 2, 3, 4, 5, 6, 7, -1, -1);
 #pragma unroll
         for (int b = 0; b < MB; ++b)
-          acc[f][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, xb[b], acc[f][b], 3, 3, 0, 127, 0, 127);
+          acc[f][b] = mfma_bf6(a, xb[b], acc[f][b]);
       }
     }
   };
@@ -223,24 +223,20 @@ constexpr NarrowTile kTiles[] = {{1, 1, 4, 3500}, {1, 2, 4, 4600}, {2, 2, 2, 490
 }  // namespace
 
 // Which tile, if any, an M x K by K x N product takes instead of the tiled
-// kernel: 0 for none, else 1 + index into kTiles.  Both sides are estimated in
-// ns from what the CU with the most tiles does (n = ceil(tiles / CUs)):
-//   narrow: its bytes at 115 per ns, plus `fixed` per round of per_cu blocks;
-//   tiled (4 waves): 6200 + 500 per 128 codes for a block alone on its CU,
-//   1000 for two; 8 waves (long K): 660 per tile and 128 codes.
-// Fitted to 165 shapes (M 1..2048, K 256..12288, N 256..12288; the choice is
-// within 1% of the best on average).  A call changes over only where the
-// estimate says at least 8% less, so that shapes near the line, and every
-// large one, stay on the tiled kernel.
+// kernel: 0 for none, else 1 + index into kTiles.  The tiled kernel's time is
+// f6_tile_bands' estimate; the narrow one's, in ns, follows from what the CU
+// with the most tiles does (n = ceil(tiles / CUs)): its bytes at 115 per ns,
+// plus `fixed` per round of per_cu blocks.  Fitted to 165 shapes (M 1..2048, K
+// 256..12288, N 256..12288).  A call takes a narrow tile only where the
+// estimate says at least 12% less, so that shapes near the line, and every
+// large one, go to the tiled kernel: over 219 shapes (M 64..9216) the choice
+// among all tiles of both kernels is within 0.9% of the best on average.
 int f6_narrow_tile(int64_t M, int64_t N, int64_t K, int64_t cus) {
   const int64_t units = (K + 127) / 128, mb = (M + 31) / 32, nb = (N + 31) / 32;
-  const bool waves8 = f6_block_waves(M, N, K, cus) == 8;
-  const int64_t tm = waves8 ? 32 * f6_tile_bands(M, N, cus) : 128;
-  const int64_t tiled_n = ((M + tm - 1) / tm * ((N + 255) / 256) + cus - 1) / cus;
-  if (tiled_n > 8) return 0;
-  const int64_t tiled = 6200 + units * (waves8 ? 660 * tiled_n : 1000 * (tiled_n / 2) + 500 * (tiled_n % 2));
+  int64_t tiled = 0;
+  f6_tile_bands(M, N, K, cus, &tiled);
   int best = 0;
-  int64_t best_ns = tiled * 92 / 100;
+  int64_t best_ns = tiled * 88 / 100;
   int i = 0;
   for (const NarrowTile& t : kTiles) {
     ++i;

@@ -157,11 +157,11 @@ __global__ __launch_bounds__(64 * W, WPS) void f6_narrow_group_kernel(
     const v8i w0 = __builtin_shufflevector(w[d][0], w[d][1], 0, 1, 2, 3, 4, 5, -1, -1);
     const v8i w1 = __builtin_shufflevector(w[d][1], w[d][2], 2, 3, 4, 5, 6, 7, -1, -1);
     v16f a[kGps];
-    a[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w0, x0, v16f{}, 3, 3, 0, 127, 0, 127);
+    a[0] = mfma_bf6(w0, x0, v16f{});
     if constexpr (G == 64)
-      a[1] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w1, x1, v16f{}, 3, 3, 0, 127, 0, 127);
+      a[1] = mfma_bf6(w1, x1, v16f{});
     else
-      a[0] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w1, x1, a[0], 3, 3, 0, 127, 0, 127);
+      a[0] = mfma_bf6(w1, x1, a[0]);
     __builtin_amdgcn_sched_barrier(0);
     store_scales((i + 1) & 1, (d + 1) & 1);
     __builtin_amdgcn_sched_barrier(0);

@@ -532,9 +532,17 @@ jq_status jq_f6_gemm_plan(int64_t M, int64_t N, int64_t K, int cus, int* waves, 
   if (waves == nullptr || tile_rows == nullptr || cus < 1) return JQ_ERR_INVALID_ARG;
   const jq_status st = check_f6_operands(M, N, K);
   if (st != JQ_OK) return st;
-  const int64_t slots = std::max<int64_t>(8, cus / 8 * 8);
-  *waves = jq::f6_block_waves(M, N, K, slots);
-  *tile_rows = 32 * (*waves == 4 ? 4 : jq::f6_tile_bands(M, N, slots));
+  // The nominal shape: 224- or 256-row tiles by the cheaper rounds (a tile
+  // costs its bands and one more), for K past 6144 or where it is 256; else
+  // 128-row tiles.
+  const int64_t per_xcd_slots = std::max<int64_t>(8, cus / 8 * 8) / 8;
+  auto cost = [&](int64_t bands) {
+    const int64_t per_xcd = ((M + 32 * bands - 1) / (32 * bands) * ((N + 255) / 256) + 7) / 8;
+    return (per_xcd + per_xcd_slots - 1) / per_xcd_slots * (bands + 1);
+  };
+  const bool full = cost(8) <= cost(7);
+  *waves = K > 6144 || full ? 8 : 4;
+  *tile_rows = *waves == 4 ? 128 : full ? 256 : 224;
   return JQ_OK;
 }
 
