@@ -1127,7 +1127,13 @@ __global__ __launch_bounds__(64 * kF6Waves, PER_CU) void w4a4_f6_gemm_kernel(
 // single k-step for G = 64, two for G = 128), then y = bf16(S + bias) (or S
 // itself, EPI kF32).  The matrix cores deliver acc_g in fp32, exactly, so the
 // fold after each group is two multiplies and an add per output: the kernel
-// is bound by that vector arithmetic, not by the MFMAs.
+// is bound by that vector arithmetic, not by the MFMAs: 48 instructions per
+// 32x32 tile and group, 208 us of it in each GEMM of the FLUX MLP at G = 64
+// (4608 x 3072 -> 12288 and back).  The walk over the groups is therefore
+// software-pipelined: read, multiply and fold in turn left a wave waiting
+// about five times per stage for LDS and the MFMAs, and addresses and the
+// joining of operand parts took a tenth of the vector instructions (309 and
+// 297 us; 274 and 272 us now; at G = 128 210 and 205 -> 195 and 196 us).
 //
 // Block tile 128 (m) x 128 (n), four waves, two blocks per CU; wave (wm, wn)
 // owns activation bands 2wm, 2wm + 1 and weight bands 2wn, 2wn + 1 of the
@@ -1135,12 +1141,12 @@ __global__ __launch_bounds__(64 * kF6Waves, PER_CU) void w4a4_f6_gemm_kernel(
 // K: both operands' fragments (activation layout and weight layout, 12 KiB
 // each) and the stage's scales (s_x and s_w of its groups, gathered from the
 // [rows, K/G] arrays by 4-byte transfers) move into LDS by buffer_load ...
-// lds, issued as instructions of their own two stages ahead into a ring of
-// three slots.  A stage waits only for its own loads (vmcnt counts the next
-// stage's as still in flight) and then meets the other waves at a barrier
-// with no memory fence, after which the slot read two stages ago takes the
-// loads of the stage two ahead.  Operand bands, rows or columns past M or N
-// read as zero (outside the buffers).
+// lds, issued as instructions of their own three stages ahead into a ring of
+// three slots.  Before a stage is read, the block waits for its loads only
+// (vmcnt counts the next stage's as still in flight) and meets at a barrier
+// with no memory fence, after which the slot of the stage before takes the
+// loads of the stage three ahead of that one.  Operand bands, rows or columns
+// past M or N read as zero (outside the buffers).
 template <int G, Epilogue EPI, bool HAS_BIAS>
 __global__ __launch_bounds__(256, 2) void w4a4g_f6_gemm_kernel(
     const uint8_t* __restrict__ xf6, const float* __restrict__ sx, int M, int mbands,
@@ -1227,26 +1233,28 @@ __global__ __launch_bounds__(256, 2) void w4a4g_f6_gemm_kernel(
 
   // Fold one group into the sums: lane holds column m = 32 (2wm + fb) +
   // (lane & 31) and rows n = 32 (2wn + f) + 8 j + 4 (lane >> 5) + r of y^T,
-  // with the lane's scales of the stage read from its scale slot.
-  float xsr[kGps][2];
-  float4 wsr[kGps][2][4];
-  auto read_scales = [&](int k) __attribute__((always_inline)) {
+  // with the lane's scales of the group read from its stage's scale slot.
+  float xsr[2][2];
+  float4 wsr[2][4];
+  const uint8_t* const opb = reinterpret_cast<const uint8_t*>(ops);
+  const uint8_t* const scb = reinterpret_cast<const uint8_t*>(scs);
+  const uint32_t x_lane = 256 * wm + 4 * (lane & 31), w_lane = 4 * kGps * 128 + 256 * wn + 16 * (lane >> 5);
+  auto read_xs = [&](int set, int k, int gl) __attribute__((always_inline)) {
+    const uint32_t xo = 4 * kScF * k + x_lane;
 #pragma unroll
-    for (int gl = 0; gl < kGps; ++gl)
-#pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        xsr[gl][b] = sck(k)[128 * gl + 32 * (2 * wm + b) + (lane & 31)];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          wsr[gl][b][j] = *reinterpret_cast<const float4*>(sck(k) + kGps * 128 + 128 * gl + 32 * (2 * wn + b) +
-                                                           8 * j + 4 * (lane >> 5));
-      }
+    for (int b = 0; b < 2; ++b) xsr[set][b] = *reinterpret_cast<const float*>(scb + (512 * gl + 128 * b) + xo);
   };
-  auto fold = [&](const v16f& acc, int f, int fb, int gl) __attribute__((always_inline)) {
-    const float xs = xsr[gl][fb];
+  auto read_ws = [&](int k, int gl, int f) __attribute__((always_inline)) {
+    const uint32_t wo = 4 * kScF * k + w_lane;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      wsr[f][j] = *reinterpret_cast<const float4*>(scb + (512 * gl + 128 * f + 32 * j) + wo);
+  };
+  auto fold = [&](const v16f& acc, int f, int fb, int set) __attribute__((always_inline)) {
+    const float xs = xsr[set][fb];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const float wsa[4] = {wsr[gl][f][j].x, wsr[gl][f][j].y, wsr[gl][f][j].z, wsr[gl][f][j].w};
+      const float wsa[4] = {wsr[f][j].x, wsr[f][j].y, wsr[f][j].z, wsr[f][j].w};
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float t = acc[4 * j + r] * xs;
@@ -1255,72 +1263,133 @@ __global__ __launch_bounds__(256, 2) void w4a4g_f6_gemm_kernel(
       }
     }
   };
+  // Fragments of a stage's slot.  The fold leaves no vector instruction to
+  // spare, so a slot costs four address registers (the rest are constants of
+  // the reads), and the 8-byte parts are relaxed atomic loads, which the
+  // compiler does not pair: a paired read needs moves to join the parts.
+  auto read8 = [&](const uint8_t* p) __attribute__((always_inline)) {
+    return __builtin_bit_cast(v2i32, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_WAVEFRONT));
+  };
+  const uint32_t xl = 4 * kFragBytes * wm + 16 * lane, xl8 = 4 * kFragBytes * wm + 8 * lane;
+  const uint32_t wl = 16 * kOpU4 + 4 * kFragBytes * wn + 16 * lane;
   auto read_x = [&](int k, int t, int fb) __attribute__((always_inline)) {
-    const uint8_t* p = reinterpret_cast<const uint8_t*>(opk(k)) + (2 * wm + fb) * 2 * kFragBytes + t * kFragBytes;
-    return join(*reinterpret_cast<const v4i32*>(p + 16 * lane), *reinterpret_cast<const v2i32*>(p + 1024 + 8 * lane));
+    const uint32_t so = 16 * 2 * kOpU4 * k;
+    const uint8_t* p = opb + (2 * kFragBytes * fb + kFragBytes * t);
+    return join(*reinterpret_cast<const v4i32*>(p + (so + xl)), read8(p + 1024 + (so + xl8)));
   };
   auto read_w = [&](int k, int t, int f) __attribute__((always_inline)) {
-    const uint8_t* p = reinterpret_cast<const uint8_t*>(opk(k) + kOpU4) + (2 * wn + f) * 2 * kFragBytes;
-    if (t == 0) {
-      const v4i32 a = *reinterpret_cast<const v4i32*>(p + 16 * lane);
-      const v2i32 b = *reinterpret_cast<const v2i32*>(p + 1024 + 16 * lane);
-      return v8i{a.x, a.y, a.z, a.w, b.x, b.y, 0, 0};
-    }
-    const v2i32 a = *reinterpret_cast<const v2i32*>(p + 1024 + 16 * lane + 8);
-    const v4i32 b = *reinterpret_cast<const v4i32*>(p + 2048 + 16 * lane);
+    const uint32_t so = 16 * 2 * kOpU4 * k + wl;
+    const uint8_t* p = opb + 2 * kFragBytes * f;
+    if (t == 0) return join(*reinterpret_cast<const v4i32*>(p + so), read8(p + 1024 + so));
+    const v2i32 a = read8(p + 1024 + 8 + so);
+    const v4i32 b = *reinterpret_cast<const v4i32*>(p + 2048 + so);
     return v8i{a.x, a.y, b.x, b.y, b.z, b.w, 0, 0};
   };
 
-  // Stage u from slot (xa, wa, sxa, swa): the stage's loads have landed
-  // and every wave has passed the barrier after them.
-  auto compute = [&](int u, int k) __attribute__((always_inline)) {
-    if constexpr (G == 64) {
+  // The walk over the groups is pipelined, so that a wave's vector unit finds
+  // the next products ready when it is done with a fold: while the products of
+  // (group, weight band 0) are folded, those of band 1 run and the next
+  // group's fragments and scales are read; while band 1's are folded, the next
+  // group's band 0 runs.
+  //   a0, a1: the products of bands 0 and 1; x, w: the group's fragments.
+  constexpr int kSteps = G / 64;  // k-steps of a group
+  v16f a0[2], a1[2];
+  v8i x[kSteps][2], w[kSteps][2];
+  auto read_group = [&](int set, int k, int gl) __attribute__((always_inline)) {
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        if (kGps * u + t >= KG) break;  // K % 128 == 64: the last stage's second half is padding
-        const v8i b0 = read_x(k, t, 0), b1 = read_x(k, t, 1);
+    for (int t = 0; t < kSteps; ++t) {
+      w[t][0] = read_w(k, kSteps * gl + t, 0);
+      x[t][0] = read_x(k, kSteps * gl + t, 0);
+      x[t][1] = read_x(k, kSteps * gl + t, 1);
+    }
+    if constexpr (G == 64) read_xs(set, k, gl);
+  };
+  auto read_w1 = [&](int k, int gl) __attribute__((always_inline)) {
 #pragma unroll
-        for (int f = 0; f < 2; ++f) {
-          const v8i a = read_w(k, t, f);
-          const v16f c0 = mfma_bf6(a, b0, v16f{});
-          const v16f c1 = mfma_bf6(a, b1, v16f{});
-          fold(c0, f, 0, t);
-          fold(c1, f, 1, t);
-        }
-      }
-    } else {
-      const v8i b00 = read_x(k, 0, 0), b01 = read_x(k, 0, 1);
-      const v8i b10 = read_x(k, 1, 0), b11 = read_x(k, 1, 1);
+    for (int t = 0; t < kSteps; ++t) w[t][1] = read_w(k, kSteps * gl + t, 1);
+  };
+  auto products = [&](v16f* a, int f) __attribute__((always_inline)) {
 #pragma unroll
-      for (int f = 0; f < 2; ++f) {
-        const v8i a0 = read_w(k, 0, f), a1 = read_w(k, 1, f);
-        v16f c0 = mfma_bf6(a0, b00, v16f{});
-        v16f c1 = mfma_bf6(a0, b01, v16f{});
-        c0 = mfma_bf6(a1, b10, c0);
-        c1 = mfma_bf6(a1, b11, c1);
-        fold(c0, f, 0, 0);
-        fold(c1, f, 1, 0);
-      }
+    for (int b = 0; b < 2; ++b) a[b] = mfma_bf6(w[0][f], x[0][b], v16f{});
+    if constexpr (kSteps == 2) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b) a[b] = mfma_bf6(w[kSteps - 1][f], x[kSteps - 1][b], a[b]);
     }
   };
-
-  // Stage u from slot u % 3: wait for its loads (those of stage u + 1, issued
-  // after them, may still be in flight: vector loads complete in order),
-  // meet the other waves (every wave is then also done with slot (u - 1) % 3,
-  // read at the previous stage), issue stage u + 2 into that slot, compute.
-  issue(0, 0);
-  if (T > 1) issue(1, 1);
-  for (int u = 0; u < T; ++u) {
-    const int k = u % 3;
-    if (u + 1 < T) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kLoads));
+  // Stage u has been read whole by this wave; make stage u + 1 readable: wait
+  // for its loads (those of stage u + 2, issued after them, may still be in
+  // flight: vector loads complete in order) and meet the other waves, after
+  // which the slot of stage u takes the loads of stage u + 3.
+  auto next_stage = [&](int u) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_waitcnt(kLgkm0);
+    if (u + 2 < T) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kLoads));
     else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __builtin_amdgcn_s_barrier();
     // no LDS read of the slot may be moved above the wait and the barrier
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
-    if (u + 2 < T) issue(u + 2, (u + 2) % 3);
-    read_scales(k);
-    compute(u, k);
+    if (u + 3 < T) issue(u + 3, u % 3);
+  };
+  // One group, the last of its stage u or not; the one after it (past the end:
+  // read, but not used) is group `gl` of slot k.
+  // The weight scales follow their folds into the same registers; the
+  // activation scales have two sets for G = 64, where a group is too short to
+  // cover a read at its end, and one for G = 128, whose fragments fill the rest.
+  auto group = [&](auto SET, bool last, int u, int k, int gl) __attribute__((always_inline)) {
+    constexpr int set = decltype(SET)::value;
+    products(a1, 1);
+    if (last) next_stage(u);
+    __builtin_amdgcn_sched_barrier(0);
+    read_group(1 - set, k, gl);
+    __builtin_amdgcn_sched_barrier(0);
+    fold(a0[0], 0, 0, set);
+    fold(a0[1], 0, 1, set);
+    __builtin_amdgcn_sched_barrier(0);
+    products(a0, 0);
+    read_w1(k, gl);
+    read_ws(k, gl, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    fold(a1[0], 1, 0, set);
+    fold(a1[1], 1, 1, set);
+    __builtin_amdgcn_sched_barrier(0);
+    read_ws(k, gl, 1);
+    if constexpr (G == 128) read_xs(set, k, gl);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  issue(0, 0);
+  if (T > 1) issue(1, 1);
+  if (T > 2) issue(2, 2);
+  if (T > 2) __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * kLoads));
+  else if (T > 1) __builtin_amdgcn_s_waitcnt(vmcnt_imm(kLoads));
+  else __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  read_group(0, 0, 0);
+  products(a0, 0);
+  read_w1(0, 0);
+  read_ws(0, 0, 0);
+  read_ws(0, 0, 1);
+  if constexpr (G == 128) read_xs(0, 0, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  using Set0 = std::integral_constant<int, 0>;
+  using Set1 = std::integral_constant<int, 1>;
+  if constexpr (G == 64) {
+    int k = 0;
+    for (int u = 0; u < T; ++u) {
+      const int kn = k == 2 ? 0 : k + 1;
+      group(Set0{}, false, u, k, 1);
+      // K % 128 == 64: the last stage's second half is padding
+      if (2 * u + 1 < KG) group(Set1{}, true, u, kn, 0);
+      k = kn;
+    }
+  } else {
+    int k = 0;
+    for (int u = 0; u < T; ++u) {
+      k = k == 2 ? 0 : k + 1;
+      group(Set0{}, true, u, k, 0);
+    }
   }
 
   if constexpr (EPI == Epilogue::kF32) {
