@@ -484,10 +484,13 @@ jq_status jq_w4a4_f6_gemm_i32(const void* xf6, int64_t M, int64_t K,
                               const void* wf6, int64_t N, int32_t* acc, void* stream);
 
 /*
- * The tile height the int8 engine's GEMM (jq_w4a4_gemm, _linear, _gemm_i32 and
- * their W1.58A4 forms) takes for an M x K by K x N product on a device with
- * `cus` compute units, for checking and tuning: *tile_rows = 128 or 112 rows
- * of activations per output tile (256 columns).  Host-only; launches nothing.
+ * The nominal tile height of the int8 engine's GEMM (jq_w4a4_gemm, _linear,
+ * _gemm_i32 and their W1.58A4 forms) for an M x K by K x N product on a device
+ * with `cus` compute units, for checking and tuning: *tile_rows = 128 or 112
+ * rows of activations per output tile (256 columns), as its int8 kernel takes
+ * them.  Products with few tiles, and most with many tiles and long K, run on
+ * kernels with tiles of their own, which the plan does not report; the results
+ * do not depend on it.  Host-only; launches nothing.
  * Errors: JQ_ERR_INVALID_ARG, JQ_ERR_UNSUPPORTED_SHAPE.
  */
 jq_status jq_gemm_plan(int64_t M, int64_t N, int64_t K, int cus, int* tile_rows);

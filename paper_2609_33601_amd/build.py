@@ -23,8 +23,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ_DIR = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libjq.so")
-SOURCES = ["quantize.hip", "ternary.hip", "gemm.hip", "gemm_narrow.hip", "gemm_group.hip", "f6.hip", "f6_narrow.hip", "f6_narrow_group.hip",
-           "f6_quant_few.hip", "jq_api.cpp"]
+SOURCES = ["quantize.hip", "ternary.hip", "gemm.hip", "gemm_narrow.hip", "gemm_wide.hip", "gemm_group.hip", "f6.hip",
+           "f6_narrow.hip", "f6_narrow_group.hip", "f6_quant_few.hip", "jq_api.cpp"]
 ARCH = "gfx950"
 
 # Per-source flags: the BF6 kernels are built without machine sinking, which

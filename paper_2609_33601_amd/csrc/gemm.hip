@@ -6,7 +6,8 @@
 //   y[m,n] = bf16_rne(((fp32(acc) * sx[m]) * sw[n]) + bias[n])
 // with every fp32 operation rounded on its own (built with -ffp-contract=off).
 //
-// Structure.  (Products with few output tiles go to gemm_narrow.hip.)
+// Structure.  (Products with few output tiles go to gemm_narrow.hip, most with
+// many tiles and long K to gemm_wide.hip.)
 //  * Block tile 128 (m) x 256 (n), four waves of 64 x 128 outputs each (a
 //    4 x 8 grid of 16 x 16 MFMA tiles, 128 int32 accumulators per lane).  A
 //    block needs 64 KiB of LDS and at most 256 registers per lane, so two
@@ -405,6 +406,8 @@ hipError_t launch_w4a4_gemm(Epilogue epi, const uint8_t* qx, const float* sx, in
   const int64_t slots = std::max<int64_t>(kNumXcd, cus / kNumXcd * kNumXcd);
   if (const int tile = gemm_narrow_tile(M, N, K, wf, slots))
     return launch_gemm_narrow(tile, epi, qx, sx, M, K, qw, sw, N, bias, out, st, wf);
+  if (const int bands = gemm_wide_bands(M, N, K, wf, slots))
+    return launch_gemm_wide(bands, epi, qx, sx, M, K, qw, sw, N, bias, out, slots, st, wf);
   const int bm = gemm_tile_rows(M, N, 2 * slots);
   const int tiles_m = static_cast<int>((M + bm - 1) / bm);
   const int tiles_n = static_cast<int>((N + kBN - 1) / kBN);

@@ -50,6 +50,14 @@ hipError_t launch_gemm_narrow(int tile, Epilogue epi, const uint8_t* qx, const f
                               const uint8_t* qw, const float* sw, int64_t N, const uint16_t* bias, void* out,
                               hipStream_t st, WeightFormat wf);
 
+// The same on the 6-bit matrix cores, operands converted inside the kernel:
+// tile height in bands of 32 rows for a product that takes it (0: none), and
+// its launch.
+int gemm_wide_bands(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus);
+hipError_t launch_gemm_wide(int bands, Epilogue epi, const uint8_t* qx, const float* sx, int64_t M, int64_t K,
+                            const uint8_t* qw, const float* sw, int64_t N, const uint16_t* bias, void* out, int64_t cus,
+                            hipStream_t st, WeightFormat wf);
+
 // Group-wise GEMM: scales sx [M, K/G] and sw [N, K/G]; epi is kBf16 or kF32.
 hipError_t launch_w4a4g_gemm(Epilogue epi, const uint8_t* qx, const float* sx, int64_t M, int64_t K, int G,
                              const uint8_t* qw, const float* sw, int64_t N, const uint16_t* bias, void* out,
