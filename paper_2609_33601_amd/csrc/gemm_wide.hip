@@ -31,9 +31,9 @@
 //   * The conversions go between the MFMAs, one (16 codes) after each pair or
 //     two of MFMAs; one barrier per step, before its last k-step, makes the
 //     next step's slot readable.
-// Rows past M or N and chunks past the end of K lie outside the buffers (or,
-// for weights, in the next row: they meet activation codes of zero) and read as
-// zero; zero codes add nothing to acc whatever they meet.
+// Rows past M or N and chunks past the end of K get an offset outside the
+// buffers (whatever the step's part of the address, which the range check
+// leaves out) and read as zero; zero codes add nothing to acc whatever they meet.
 //
 // What bounds it.  Per step of a 256 x 256 tile a SIMD has 64 MFMAs (2048
 // clocks) and about 600 other instructions to issue at 4.5 clocks each, one
@@ -208,9 +208,10 @@ __global__ __launch_bounds__(64 * kWaves, 1) void w4a4_wide_kernel(
 
   uint4 w[2][kWL];
   auto load_w = [&](uint32_t wo, int ks, int f, int q) __attribute__((always_inline)) {
-    w[f][q] = __builtin_bit_cast(
-        uint4, __builtin_amdgcn_raw_buffer_load_b128(rsw, wo + static_cast<uint32_t>(32 * f) * wrow_bytes + 32 * q,
-                                                     (kTern ? 64 : 128) * ks, 0));
+    constexpr int kStep = kTern ? 64 : 128;
+    uint32_t o = wo + static_cast<uint32_t>(32 * f) * wrow_bytes + 32 * q;
+    if (KTAIL && static_cast<uint32_t>(kStep * ks + 16 * lh + 32 * q) >= wrow_bytes) o = kOutsideOperand;
+    w[f][q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsw, o, kStep * ks, 0));
   };
   int cs[2] = {0, 0}, lead[2] = {0, 0};  // sums of the columns' codes; those of the next step's first k-step
   v8i aw[2][2];                          // [k-step parity][band]
