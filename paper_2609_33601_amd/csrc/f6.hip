@@ -1506,26 +1506,28 @@ int64_t f6_operand_bytes(int64_t rows, int64_t K) { return (rows + 31) / 32 * f6
 
 // The GEMM's tile height in bands of 32 rows, 5 .. 8 (one block per CU) or 4
 // (two), and the estimate in ns it was picked by, for the XCD with most tiles:
-//   one block per CU: its rounds, each 38 b + 314 ns per 128 codes and 1080 b
+//   one block per CU: its rounds, each 38 b + 280 ns per 128 codes and 1080 b
 //   for the epilogue (b bands);
-//   two blocks per CU: 800 ns per 128 codes and 5600 for each round of two
-//   tiles per CU, 420 and 4300 for a last round with one tile per CU or fewer.
-// Fitted to 130 shapes of 768 tokens and more (K 1024..15360, N 1024..12288).
-// Over those and 89 smaller ones the pick is within 0.8% of the best height on
-// average; always the two-block shape or 224/256-row tiles by the rounds
-// alone, which was the rule before, is 10% off.
+//   two blocks per CU: 720 ns per 128 codes and 5600 for each round of two
+//   tiles per CU, 378 and 4300 for a last round with one tile per CU or fewer.
+// Fitted to 187 shapes (M 768..9216, K 128..15360, N 1024..12288) on codes of
+// a heavy-tailed activation (Student t, 3 degrees of freedom): the pick is
+// within 0.25% of the best height on average.  On codes of a Gaussian one,
+// which the card runs up to a third slower, and down to 64 tokens with the
+// few-tile kernel beside it, within 0.75%; the rule before (two blocks, or
+// 224/256-row tiles by the rounds alone) was 10% off.
 int f6_tile_bands(int64_t M, int64_t N, int64_t K, int64_t slots, int64_t* ns) {
   const int64_t tiles_n = (N + kFBN - 1) / kFBN, T = (K + 127) / 128;
   const int64_t cus = std::max<int64_t>(1, slots / kNumXcd);  // of an XCD
   auto per_xcd = [&](int b) { return ((M + 32 * b - 1) / (32 * b) * tiles_n + kNumXcd - 1) / kNumXcd; };
   const int64_t n4 = per_xcd(4), rest = n4 % (2 * cus);
-  const int64_t round2 = 800 * T + 5600;
+  const int64_t round2 = 720 * T + 5600;
   int best = 4;
   int64_t best_ns = n4 / (2 * cus) * round2;
   if (rest > cus) best_ns += round2;
-  else if (rest > 0) best_ns += 420 * T + 4300;
+  else if (rest > 0) best_ns += 378 * T + 4300;
   for (int b = 8; b >= 5; --b) {
-    const int64_t t = (per_xcd(b) + cus - 1) / cus * (T * (38 * b + 314) + 1080 * b);
+    const int64_t t = (per_xcd(b) + cus - 1) / cus * (T * (38 * b + 280) + 1080 * b);
     if (t < best_ns) best = b, best_ns = t;
   }
   if (ns != nullptr) *ns = best_ns;

@@ -23,10 +23,10 @@ torch = pytest.importorskip("torch")
 # bands, M, K, N, bias
 SHAPES = [
     (4, 1056, 128, 1241, True), (4, 5457, 256, 2819, False), (4, 5401, 384, 5907, True), (4, 4225, 640, 4680, True),
-    (5, 5387, 128, 1285, True), (5, 5427, 256, 1352, True), (5, 5422, 320, 1295, False), (5, 5939, 640, 2587, True),
+    (5, 5387, 128, 1285, True), (5, 5427, 256, 1352, True), (5, 5422, 320, 1295, False), (5, 5400, 1088, 2819, True),
     (5, 5022, 3072, 3078, True),
-    (6, 5918, 448, 1541, True), (6, 4366, 640, 5552, False), (6, 5891, 3072, 5391, True), (6, 5865, 3008, 3352, True),
-    (7, 4909, 1088, 2315, True), (7, 4613, 1152, 5192, True), (7, 4909, 3008, 4913, False),
+    (6, 5925, 576, 1577, True), (6, 4366, 640, 5552, False), (6, 5891, 3072, 5391, True), (6, 4378, 3008, 5384, True),
+    (7, 5398, 1664, 4360, True), (7, 4225, 1856, 5640, True), (7, 4909, 3008, 4913, False),
     (8, 2693, 3008, 4865, True), (8, 5853, 3072, 4616, False), (8, 4096, 3200, 4096, True),
 ]
 
