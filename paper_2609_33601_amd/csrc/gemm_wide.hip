@@ -452,6 +452,14 @@ __global__ __launch_bounds__(64 * kWaves, 1) void w4a4_wide_kernel(
               if constexpr (q % 2 == 1) load_x(x2, k2, q / 2);
             }
           });
+          // Five vector instructions between the two MFMAs rather than all after
+          // the second (4608 x 12288 -> 3072 at 8 bands 112 -> 103 us, at 7 97 ->
+          // 96; ternary weights 104 -> 102.5 at 7, but 113 -> 115 at 8).
+          if constexpr (!kTern || NFM < 8) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          }
           __builtin_amdgcn_sched_barrier(0);
         });
         if constexpr (s == 2) {
