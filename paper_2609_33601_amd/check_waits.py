@@ -17,6 +17,12 @@ number of younger operations issued after it on any path (a vmcnt(N) wait
 retires a load once at least N younger operations follow it).  Loads into
 LDS (``... lds``) have no destination registers; stores and scratch accesses
 count towards vmcnt like loads.
+
+The compiler does not look into inline asm for the wait states that gfx950
+wants between two dependent instructions either, so every kernel of the file is
+checked for the two that its asm can miss (`wait_states`): one between a write
+of M0 and a transfer to LDS, and five between a vector instruction's write of a
+scalar register and a vector-memory instruction that reads it.
 """
 
 import re
@@ -152,6 +158,67 @@ def hazards(lines):
     return [(ln, s, load_ln) for (ln, load_ln), s in sorted(found.items())]
 
 
+_SGPR_RANGE = re.compile(r"\bs\[(\d+):(\d+)\]")
+_SGPR_SINGLE = re.compile(r"\bs(\d+)\b")
+_M0_STATES, _SGPR_STATES = 1, 5
+
+
+def scalars(text):
+    """The indices of the scalar registers named in an operand string."""
+    out = set()
+    for m in _SGPR_RANGE.finditer(text):
+        out |= set(range(int(m.group(1)), int(m.group(2)) + 1))
+    return out | {int(m.group(1)) for m in _SGPR_SINGLE.finditer(_SGPR_RANGE.sub("", text))}
+
+
+def _wait_step(state, ln, s, found):
+    """Apply one instruction to {"m0" or scalar register: wait states still missing}."""
+    op = s.split()[0]
+    args = s[len(op):]
+    parts = [a.strip() for a in args.split(",")]
+    if op.startswith(_VMEM_PREFIXES + ("flat_",)):
+        if "m0" in state and re.search(r"\blds\b", args):
+            found[ln] = (s, "m0")
+        early = scalars(args) & state.keys()
+        if early:
+            found[ln] = (s, f"s{max(early)}")
+    passed = int(parts[0], 0) + 1 if op == "s_nop" else 1
+    state = {k: n - passed for k, n in state.items() if n > passed}
+    if parts[0] == "m0":
+        state["m0"] = _M0_STATES
+    if op.startswith("v_"):
+        # carry-outs and v_div_scale name a second scalar destination
+        dest = scalars(parts[0]) | (scalars(parts[1]) if len(parts) > 1 and ("_co_" in op or "div_scale" in op) else set())
+        for r in dest:
+            state[r] = _SGPR_STATES
+    return state
+
+
+def wait_states(lines):
+    """Vector-memory instructions of one kernel that miss a wait state on some path.
+
+    Returns (line number, instruction, register) triples; the register is "m0" or a scalar register."""
+    blocks = _blocks(lines)
+    if not blocks:
+        return []
+    entry = [None] * len(blocks)
+    entry[0] = {}
+    found = {}
+    work = [0]
+    while work:
+        i = work.pop()
+        state = entry[i]
+        for ln, s in blocks[i][1]:
+            state = _wait_step(state, ln, s, found)
+        for j in blocks[i][2]:
+            old = entry[j]
+            new = dict(state) if old is None else {k: max(state.get(k, 0), old.get(k, 0)) for k in state.keys() | old.keys()}
+            if new != old:
+                entry[j] = new
+                work.append(j)
+    return [(ln, s, r) for ln, (s, r) in sorted(found.items())]
+
+
 def kernels(asm_text, pattern):
     """(name, [(line number, text)]) of every kernel whose symbol matches `pattern`.
 
@@ -177,7 +244,8 @@ def kernels(asm_text, pattern):
 
 
 def check_asm(asm_text, pattern="w4a4_f6_gemm_kernel"):
-    """Raise RuntimeError naming the first hazards found in the matching kernels."""
+    """Raise RuntimeError naming the first hazards found: loads touched before their wait in the
+    matching kernels, missing wait states in any."""
     ks = kernels(asm_text, pattern)
     if not ks:
         raise RuntimeError(f"no kernel matching {pattern!r} in the assembly")
@@ -185,6 +253,9 @@ def check_asm(asm_text, pattern="w4a4_f6_gemm_kernel"):
     for name, lines in ks:
         for ln, ins, load_ln in hazards(lines):
             problems.append(f"{name}: line {ln} '{ins}' touches the registers of the load at line {load_ln}")
+    for name, lines in kernels(asm_text, ""):
+        for ln, ins, reg in wait_states(lines):
+            problems.append(f"{name}: line {ln} '{ins}' follows the write of {reg} too closely")
     if problems:
         raise RuntimeError("vector-load ordering check failed:\n" + "\n".join(problems[:10]))
     return len(ks)

@@ -637,6 +637,13 @@ __device__ __forceinline__ void static_for(F&& f) {
 // alongside), so that the compiler neither tracks them nor orders LDS reads
 // behind them: the GEMM orders them against its LDS reads with its own
 // explicit waits, and is the only user of M0 in its kernel.
+// The wait states that the compiler would put between two dependent
+// instructions are its users' to keep as well: one between a write of M0 and a
+// transfer to LDS, five between a vector instruction's write of a scalar
+// register (v_readlane of a spilled one, say) and a memory instruction's read
+// of it.  The first is in dma16_raw and dma4_raw, the second in dma4_raw, whose
+// descriptors may be spilled; the build checks both over the whole file
+// (check_waits.py).
 typedef unsigned v4u32r __attribute__((ext_vector_type(4)));
 struct RawRsrc {
   v4u32r w;  // the four descriptor words of a raw (unswizzled, stride 0) buffer
@@ -655,7 +662,7 @@ __device__ __forceinline__ uint32_t lds_addr(const void* p) {
 // OFFSET (an instruction immediate) moves both the source and the target.
 template <int OFFSET = 0>
 __device__ __forceinline__ void dma16_raw(const RawRsrc& r, uint32_t lds, uint32_t voffset, uint32_t soffset) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen offset:%4 lds"
                :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voffset), "s"(r.w), "s"(soffset), "n"(OFFSET)
                : "memory");
 }
@@ -668,7 +675,7 @@ __device__ __forceinline__ v4i32 load16_raw(const RawRsrc& r, uint32_t voffset, 
   return v;
 }
 __device__ __forceinline__ void dma4_raw(const RawRsrc& r, uint32_t lds, uint32_t voffset) {
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dword %1, %2, 0 offen lds"
                :: "s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voffset), "s"(r.w) : "memory");
 }
 

@@ -1,7 +1,11 @@
 """The build's check of the BF6 GEMM's hand-ordered vector loads
 (check_waits.py), on hand-written assembly: along every control-flow path it
 must flag each touch of a load's destination registers that no vmcnt wait has
-retired, and nothing else."""
+retired, and each vector-memory instruction that misses a wait state after the
+write of M0 or of a scalar register it reads, and nothing else; and on the
+assembly of the last build, which must be clean."""
+
+import os
 
 import pytest
 
@@ -99,3 +103,42 @@ def test_check_asm_raises_and_counts():
     assert check_waits.check_asm(HEAD + "\ts_nop 0\n" + TAIL) == 1
     with pytest.raises(RuntimeError, match="no kernel"):
         check_waits.check_asm("foo:\n\ts_endpgm\n")
+
+
+def states(body):
+    return [r for _, _, r in check_waits.wait_states(check_waits.kernels(HEAD + body + TAIL, "")[0][1])]
+
+
+def test_transfer_to_lds_right_after_m0_is_flagged():
+    load = "\tbuffer_load_dwordx4 v4, s[0:3], s6 offen lds\n"
+    assert states("\ts_mov_b32 m0, s5\n" + load) == ["m0"]
+    assert states("\ts_mov_b32 m0, s5\n\ts_nop 0\n" + load + load) == []
+    # an ordinary load does not read M0; the write may be in the block before
+    assert states("\ts_mov_b32 m0, s5\n\tbuffer_load_dword v1, v4, s[0:3], s6 offen\n") == []
+    assert states("\ts_cbranch_scc1 .LBB0_2\n\ts_mov_b32 m0, s5\n.LBB0_2:\n" + load) == ["m0"]
+
+
+def test_memory_read_of_a_vector_written_scalar_is_flagged():
+    load = "\tbuffer_load_dword v0, s[8:11], 0 offen lds\n"
+    back = "".join(f"\tv_readlane_b32 s{8 + i}, v255, {i}\n" for i in range(4))
+    assert states(back + "\ts_mov_b32 m0, s49\n\ts_nop 2\n" + load) == ["s11"]
+    assert states(back + "\ts_mov_b32 m0, s49\n\ts_nop 3\n" + load) == []
+    assert states("\tv_readfirstlane_b32 s6, v1\n\ts_nop 4\n\tbuffer_load_dword v1, v4, s[0:3], s6 offen\n") == []
+    # a scalar instruction's write needs none
+    assert states("\ts_add_u32 s6, s7, s8\n\tbuffer_load_dword v1, v4, s[0:3], s6 offen\n") == []
+
+
+def test_check_asm_raises_on_a_missing_wait_state():
+    with pytest.raises(RuntimeError, match="write of m0"):
+        check_waits.check_asm(HEAD + "\ts_mov_b32 m0, s5\n\tbuffer_load_dword v4, s[0:3], 0 offen lds\n" + TAIL)
+
+
+def test_the_last_build_is_clean():
+    from paper_2609_33601_amd import build
+
+    for source, pattern in build.CHECKED_SOURCES.items():
+        path = os.path.join(build.OBJ_DIR, os.path.splitext(source)[0] + ".s")
+        if not os.path.exists(path):
+            pytest.skip("no assembly of the last build here")
+        with open(path) as f:
+            assert check_waits.check_asm(f.read(), pattern) > 0
