@@ -485,26 +485,21 @@ jq_status jq_w4a4_f6_gemm_i32(const void* xf6, int64_t M, int64_t K,
                               const void* wf6, int64_t N, int32_t* acc, void* stream);
 
 /*
- * The nominal tile height of the int8 engine's GEMM (jq_w4a4_gemm, _linear,
- * _gemm_i32 and their W1.58A4 forms) for an M x K by K x N product on a device
- * with `cus` compute units, for checking and tuning: *tile_rows = 128 or 112
- * rows of activations per output tile (256 columns), as its int8 kernel takes
- * them.  Products with few tiles, and most with many tiles and long K, run on
- * kernels with tiles of their own, which the plan does not report; the results
- * do not depend on it.  Host-only; launches nothing.
+ * The tile height that the packed engine's GEMM (jq_w4a4_gemm, _linear,
+ * _gemm_i32) takes for an M x K by K x N product on a device with `cus` compute
+ * units, for checking and tuning: *tile_rows = 32 or 64 rows of activations per
+ * output tile (few tiles), 112 or 128 (the int8 kernel), or 192, 224 or 256 (the
+ * 6-bit kernel for many tiles and long K).  A W1.58A4 product may take another
+ * of these.  Host-only; launches nothing.
  * Errors: JQ_ERR_INVALID_ARG, JQ_ERR_UNSUPPORTED_SHAPE.
  */
 jq_status jq_gemm_plan(int64_t M, int64_t N, int64_t K, int cus, int* tile_rows);
 
 /*
- * The nominal block shape of the BF6 GEMM (jq_w4a4_f6_gemm, _linear, _gemm_i32)
- * for an M x K by K x N product on a device with `cus` compute units, by which
- * products can be told apart in checks and tuning: *waves = 8 (one large tile
- * per CU at a time) or 4 (two small ones), *tile_rows = the rows of activations
- * per output tile (256 columns).  The kernels that run refine it: tiles of 128
- * to 256 rows by the least estimated time, and smaller ones for products with
- * too few of those to fill the device (few tokens, narrow weights).  The plan
- * does not report that choice, and the results do not depend on it.
+ * The block shape that the BF6 GEMM (jq_w4a4_f6_gemm, _linear, _gemm_i32) takes
+ * for an M x K by K x N product on a device with `cus` compute units, for
+ * checking and tuning: *waves per block, *tile_rows = the rows of activations
+ * per output tile, 32 or 64 (few tiles) or 128 to 256 in steps of 32.
  * Host-only; launches nothing.
  * Errors: JQ_ERR_INVALID_ARG, JQ_ERR_UNSUPPORTED_SHAPE.
  */

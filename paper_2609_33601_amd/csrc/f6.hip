@@ -1541,6 +1541,22 @@ int f6_tile_bands(int64_t M, int64_t N, int64_t K, int64_t slots, int64_t* ns) {
   return best;
 }
 
+GemmRoute f6_route(int64_t M, int64_t N, int64_t K, int64_t cus) {
+  GemmRoute r{GemmKernel::kTiled, 0, kF6Waves, 0, kFBN};
+  if ((r.pick = f6_narrow_tile(M, N, K, cus)) != 0) {
+    r.kernel = GemmKernel::kNarrow;
+    f6_narrow_shape(r.pick, &r.rows, &r.cols);
+  } else {
+    r.rows = 32 * f6_tile_bands(M, N, K, cus, nullptr);
+  }
+  return r;
+}
+
+GemmRoute f6_group_route(int64_t M, int64_t N, int64_t K, int G, int64_t cus) {
+  if (const int waves = f6_narrow_group_waves(M, N, K, G, cus)) return {GemmKernel::kNarrow, 0, waves, 32, 32};
+  return {GemmKernel::kTiled, 0, 4, 128, 128};
+}
+
 template <int G>
 hipError_t launch_quantize_f6(const uint16_t* x, int64_t M, int64_t K, uint8_t* out, float* scale, hipStream_t st) {
   if (f6_quantize_few_rows(M)) return launch_quantize_few_f6(x, M, K, G, out, scale, st);
@@ -1629,13 +1645,12 @@ hipError_t launch_quantize_groups_f6(const uint16_t* x, int64_t M, int64_t K, in
 hipError_t launch_w4a4g_f6_gemm(Epilogue epi, const uint8_t* xf6, const float* sx, int64_t M, int64_t K, int G,
                                 const uint8_t* wf6, const float* sw, int64_t N, const uint16_t* bias, void* out,
                                 hipStream_t st) {
-  int dev = 0, cus = 0;
-  hipError_t e = hipGetDevice(&dev);
+  int64_t cus = 0;
+  const hipError_t e = device_route_cus(&cus);
   if (e != hipSuccess) return e;
-  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
-  if (const int waves = f6_narrow_group_waves(M, N, K, G, std::max<int64_t>(kNumXcd, cus / kNumXcd * kNumXcd)))
-    return launch_f6_narrow_group(waves, epi, xf6, sx, M, K, G, wf6, sw, N, bias, out, st);
+  const GemmRoute r = f6_group_route(M, N, K, G, cus);
+  if (r.kernel == GemmKernel::kNarrow)
+    return launch_f6_narrow_group(r.waves, epi, xf6, sx, M, K, G, wf6, sw, N, bias, out, st);
   const int ksteps = static_cast<int>(f6_ksteps(K));
   const int tiles_m = static_cast<int>((M + 127) / 128), tiles_n = static_cast<int>((N + 127) / 128);
   const int64_t tiles = static_cast<int64_t>(tiles_m) * tiles_n;
@@ -1681,16 +1696,14 @@ hipError_t launch_int4_to_f6(const uint8_t* q, int64_t rows, int64_t K, uint8_t*
 hipError_t launch_w4a4_f6_gemm(Epilogue epi, const uint8_t* xf6, const float* sx, int64_t M, int64_t K,
                                const uint8_t* wf6, const float* sw, int64_t N, const uint16_t* bias, void* out,
                                hipStream_t st) {
-  int dev = 0, cus = 0;
-  hipError_t e = hipGetDevice(&dev);
+  int64_t slots = 0;
+  const hipError_t e = device_route_cus(&slots);
   if (e != hipSuccess) return e;
-  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
+  const GemmRoute r = f6_route(M, N, K, slots);
+  if (r.kernel == GemmKernel::kNarrow)
+    return launch_f6_narrow(r.pick, epi, xf6, sx, M, K, wf6, sw, N, bias, out, st);
   const int ksteps = static_cast<int>(f6_ksteps(K));
-  const int64_t slots = std::max<int64_t>(kNumXcd, cus / kNumXcd * kNumXcd);
-  if (const int tile = f6_narrow_tile(M, N, K, slots))
-    return launch_f6_narrow(tile, epi, xf6, sx, M, K, wf6, sw, N, bias, out, st);
-  const int bands = f6_tile_bands(M, N, K, slots, nullptr);
+  const int bands = r.rows / 32;
   const int tiles_m = static_cast<int>((M + 32 * bands - 1) / (32 * bands));
   const int tiles_n = static_cast<int>((N + kFBN - 1) / kFBN);
   const int64_t per_xcd = (static_cast<int64_t>(tiles_m) * tiles_n + kNumXcd - 1) / kNumXcd;

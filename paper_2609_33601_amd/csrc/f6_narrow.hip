@@ -247,6 +247,11 @@ int f6_narrow_tile(int64_t M, int64_t N, int64_t K, int64_t cus) {
   return best;
 }
 
+void f6_narrow_shape(int tile, int* rows, int* cols) {
+  *rows = 32 * kTiles[tile - 1].mb;
+  *cols = 32 * kTiles[tile - 1].nb;
+}
+
 hipError_t launch_f6_narrow(int tile, Epilogue epi, const uint8_t* xf6, const float* sx, int64_t M, int64_t K,
                             const uint8_t* wf6, const float* sw, int64_t N, const uint16_t* bias, void* out,
                             hipStream_t st) {

@@ -395,20 +395,41 @@ int gemm_tile_rows(int64_t M, int64_t N, int64_t slots) {
   return best;
 }
 
+GemmRoute gemm_route(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus) {
+  GemmRoute r{GemmKernel::kTiled, 0, kThreads / 64, 0, kBN};
+  if ((r.pick = gemm_narrow_tile(M, N, K, wf, cus)) != 0) {
+    r.kernel = GemmKernel::kNarrow;
+    gemm_narrow_shape(r.pick, &r.rows, &r.cols);
+  } else if ((r.pick = gemm_wide_bands(M, N, K, wf, cus)) != 0) {
+    r.kernel = GemmKernel::kWide;
+    r.rows = 32 * r.pick;
+  } else {
+    r.rows = gemm_tile_rows(M, N, 2 * cus);
+  }
+  return r;
+}
+
+hipError_t device_route_cus(int64_t* cus) {
+  int dev = 0, n = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
+  *cus = route_cus(n);
+  return e;
+}
+
 hipError_t launch_w4a4_gemm(Epilogue epi, const uint8_t* qx, const float* sx, int64_t M, int64_t K,
                             const uint8_t* qw, const float* sw, int64_t N, const uint16_t* bias,
                             void* out, hipStream_t st, WeightFormat wf) {
-  int dev = 0, cus = 0;
-  hipError_t e = hipGetDevice(&dev);
+  int64_t cus = 0;
+  const hipError_t e = device_route_cus(&cus);
   if (e != hipSuccess) return e;
-  e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
-  const int64_t slots = std::max<int64_t>(kNumXcd, cus / kNumXcd * kNumXcd);
-  if (const int tile = gemm_narrow_tile(M, N, K, wf, slots))
-    return launch_gemm_narrow(tile, epi, qx, sx, M, K, qw, sw, N, bias, out, st, wf);
-  if (const int bands = gemm_wide_bands(M, N, K, wf, slots))
-    return launch_gemm_wide(bands, epi, qx, sx, M, K, qw, sw, N, bias, out, slots, st, wf);
-  const int bm = gemm_tile_rows(M, N, 2 * slots);
+  const GemmRoute r = gemm_route(M, N, K, wf, cus);
+  if (r.kernel == GemmKernel::kNarrow)
+    return launch_gemm_narrow(r.pick, epi, qx, sx, M, K, qw, sw, N, bias, out, st, wf);
+  if (r.kernel == GemmKernel::kWide)
+    return launch_gemm_wide(r.pick, epi, qx, sx, M, K, qw, sw, N, bias, out, cus, st, wf);
+  const int bm = r.rows;
   const int tiles_m = static_cast<int>((M + bm - 1) / bm);
   const int tiles_n = static_cast<int>((N + kBN - 1) / kBN);
   const int64_t T = static_cast<int64_t>(tiles_m) * tiles_n;

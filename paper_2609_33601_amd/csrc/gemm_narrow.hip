@@ -242,6 +242,11 @@ int gemm_narrow_tile(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t c
   return best;
 }
 
+void gemm_narrow_shape(int tile, int* rows, int* cols) {
+  *rows = 32 * kTiles[tile - 1].mb;
+  *cols = 32 * kTiles[tile - 1].nb;
+}
+
 hipError_t launch_gemm_narrow(int tile, Epilogue epi, const uint8_t* qx, const float* sx, int64_t M, int64_t K,
                               const uint8_t* qw, const float* sw, int64_t N, const uint16_t* bias, void* out,
                               hipStream_t st, WeightFormat wf) {

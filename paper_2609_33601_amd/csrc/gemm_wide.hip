@@ -514,7 +514,9 @@ int gemm_wide_bands(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cu
   for (const int64_t rows : {128, 112}) {
     const int64_t n = per_xcd(rows), rest = n % (2 * xcd_cus);
     const int64_t rounds = 100 * (n / (2 * xcd_cus)) + (rest == 0 ? 0 : rest <= xcd_cus ? 67 : 100);
-    const int64_t ns = rounds * (rows == 128 ? 100 : 93) * (1190 * ((K + 127) / 128) + 10500) / 10000;
+    // 128 bits: a plan may be asked for sizes that no launch accepts
+    const int64_t ns = static_cast<int64_t>(static_cast<__int128>(rounds) * (rows == 128 ? 100 : 93) *
+                                            (1190 * ((K + 127) / 128) + 10500) / 10000);
     if (best_ns < 0 || ns < best_ns) best_ns = ns;
   }
   best_ns = best_ns * 90 / 100;

@@ -524,7 +524,7 @@ jq_status jq_gemm_plan(int64_t M, int64_t N, int64_t K, int cus, int* tile_rows)
   if (st != JQ_OK) return st;
   st = check_shape(N, K);
   if (st != JQ_OK) return st;
-  *tile_rows = jq::gemm_tile_rows(M, N, 2 * std::max<int64_t>(8, cus / 8 * 8));
+  *tile_rows = jq::gemm_route(M, N, K, jq::WeightFormat::kInt4, jq::route_cus(cus)).rows;
   return JQ_OK;
 }
 
@@ -532,18 +532,27 @@ jq_status jq_f6_gemm_plan(int64_t M, int64_t N, int64_t K, int cus, int* waves, 
   if (waves == nullptr || tile_rows == nullptr || cus < 1) return JQ_ERR_INVALID_ARG;
   const jq_status st = check_f6_operands(M, N, K);
   if (st != JQ_OK) return st;
-  // The nominal shape: 224- or 256-row tiles by the cheaper rounds (a tile
-  // costs its bands and one more), for K past 6144 or where it is 256; else
-  // 128-row tiles.
-  const int64_t per_xcd_slots = std::max<int64_t>(8, cus / 8 * 8) / 8;
-  auto cost = [&](int64_t bands) {
-    const int64_t per_xcd = ((M + 32 * bands - 1) / (32 * bands) * ((N + 255) / 256) + 7) / 8;
-    return (per_xcd + per_xcd_slots - 1) / per_xcd_slots * (bands + 1);
-  };
-  const bool full = cost(8) <= cost(7);
-  *waves = K > 6144 || full ? 8 : 4;
-  *tile_rows = *waves == 4 ? 128 : full ? 256 : 224;
+  const jq::GemmRoute r = jq::f6_route(M, N, K, jq::route_cus(cus));
+  *waves = r.waves;
+  *tile_rows = r.rows;
   return JQ_OK;
+}
+
+int jq_internal_route(int kind, int64_t M, int64_t N, int64_t K, int G, int cus, int out[4]) {
+  const int64_t c = jq::route_cus(cus);
+  jq::GemmRoute r;
+  switch (kind) {
+    case JQ_ROUTE_W4A4: r = jq::gemm_route(M, N, K, jq::WeightFormat::kInt4, c); break;
+    case JQ_ROUTE_W158A4: r = jq::gemm_route(M, N, K, jq::WeightFormat::kTernary, c); break;
+    case JQ_ROUTE_W4A4_F6: r = jq::f6_route(M, N, K, c); break;
+    case JQ_ROUTE_W4A4G_F6: r = jq::f6_group_route(M, N, K, G, c); break;
+    default: return 1;
+  }
+  out[0] = static_cast<int>(r.kernel);
+  out[1] = r.waves;
+  out[2] = r.rows;
+  out[3] = r.cols;
+  return 0;
 }
 
 }  // extern "C"

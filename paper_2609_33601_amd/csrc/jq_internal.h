@@ -38,14 +38,31 @@ enum class WeightFormat { kInt4, kTernary };
 hipError_t launch_w4a4_gemm(Epilogue epi, const uint8_t* qx, const float* sx, int64_t M, int64_t K,
                             const uint8_t* qw, const float* sw, int64_t N, const uint16_t* bias,
                             void* out, hipStream_t st, WeightFormat wf = WeightFormat::kInt4);
-// Its tile height (128 or 112 activation rows) for an M x N output with
-// `slots` block slots (two per CU).
+// Which kernel and tile an M x K by K x N product takes on a device with `cus`
+// CUs: what the launchers go by, and the plan queries report.
+enum class GemmKernel { kTiled = 0, kNarrow = 1, kWide = 2 };
+struct GemmRoute {
+  GemmKernel kernel;
+  int pick;               // the narrow kernel's tile, the wide kernel's bands
+  int waves, rows, cols;  // of a block; activation rows and columns of its tile
+};
+GemmRoute gemm_route(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus);
+GemmRoute f6_route(int64_t M, int64_t N, int64_t K, int64_t cus);
+GemmRoute f6_group_route(int64_t M, int64_t N, int64_t K, int G, int64_t cus);
+// The CUs that the rules count with: whole ones per XCD.
+inline int64_t route_cus(int64_t cus) { return cus / 8 * 8 > 8 ? cus / 8 * 8 : 8; }
+// The current device's.
+hipError_t device_route_cus(int64_t* cus);
+
+// The tiled kernel's tile height (128 or 112 activation rows) for an M x N
+// output with `slots` block slots (two per CU).
 int gemm_tile_rows(int64_t M, int64_t N, int64_t slots);
 
 // Its kernel for products with few output tiles: which of its tiles an M x K
 // by K x N product on `cus` CUs takes (0: none, it goes to the tiled kernel),
 // and its launch.
 int gemm_narrow_tile(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus);
+void gemm_narrow_shape(int tile, int* rows, int* cols);
 hipError_t launch_gemm_narrow(int tile, Epilogue epi, const uint8_t* qx, const float* sx, int64_t M, int64_t K,
                               const uint8_t* qw, const float* sw, int64_t N, const uint16_t* bias, void* out,
                               hipStream_t st, WeightFormat wf);
@@ -76,6 +93,7 @@ int f6_tile_bands(int64_t M, int64_t N, int64_t K, int64_t slots, int64_t* ns);
 // M x K by K x N product on `cus` CUs takes (0: none, it goes to the tiled
 // kernel), and its launch.
 int f6_narrow_tile(int64_t M, int64_t N, int64_t K, int64_t cus);
+void f6_narrow_shape(int tile, int* rows, int* cols);
 hipError_t launch_f6_narrow(int tile, Epilogue epi, const uint8_t* xf6, const float* sx, int64_t M, int64_t K,
                             const uint8_t* wf6, const float* sw, int64_t N, const uint16_t* bias, void* out,
                             hipStream_t st);
@@ -131,5 +149,11 @@ hipError_t launch_w4a4_f6_gemm(Epilogue epi, const uint8_t* xf6, const float* sx
 hipError_t noalloc_scratch(void** ptr);
 
 }  // namespace jq
+
+// For the tests only (no part of the C ABI): the route of a product of one of
+// the kinds below, as {kernel, waves, tile rows, tile columns}.  Returns 0, or
+// 1 for a kind that does not exist.  Sizes are not checked.
+enum { JQ_ROUTE_W4A4 = 0, JQ_ROUTE_W158A4 = 1, JQ_ROUTE_W4A4_F6 = 2, JQ_ROUTE_W4A4G_F6 = 3 };
+extern "C" int jq_internal_route(int kind, int64_t M, int64_t N, int64_t K, int G, int cus, int out[4]);
 
 #endif  // JQ_INTERNAL_H

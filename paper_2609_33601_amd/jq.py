@@ -401,7 +401,7 @@ def jq_w4a4_f6_workspace_bytes(M, K):
 
 
 def jq_gemm_plan(M, N, K, cus):
-    """Tile rows (128 or 112) the int8 engine's GEMM takes for an M x K by K x N product on `cus` CUs (host only)."""
+    """Tile rows the packed engine's int4 GEMM takes for an M x K by K x N product on `cus` CUs (host only)."""
     t = ctypes.c_int(0)
     st = lib().jq_gemm_plan(int(M), int(N), int(K), int(cus), ctypes.byref(t))
     _check(st, "jq_gemm_plan")

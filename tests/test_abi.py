@@ -12,6 +12,7 @@ import re
 import pytest
 
 from paper_2609_33601_amd import jq
+from tests.routes import route
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "jq.h")
@@ -305,19 +306,20 @@ def test_group_f6_validation():
 
 
 def test_gemm_plan():
-    """The int8 GEMM's tile height: 112 rows where 128-row tiles would leave
-    the last round of blocks mostly empty and 112-row tiles fill it, else 128."""
+    """The packed engine's tile height is that of the kernel which the product takes."""
     plan = lambda M, N, K: jq.jq_gemm_plan(M, N, K, 256)
-    assert plan(9216, 3072, 12288) == 112   # FLUX MLP-down: 864 tiles -> 996 (two full rounds of 512)
-    assert plan(4608, 3072, 12288) == 112   # FLUX MLP-down, one image: 432 -> 504 of 512 slots
-    assert plan(4608, 12288, 3072) == 128   # FLUX MLP-up: the last 128-row round is three-eighths full
-    assert plan(4608, 3072, 3072) == 112    # DiT attention projection
-    assert plan(4608, 9216, 3072) == 112    # DiT fused QKV
-    assert plan(4096, 12288, 4096) == 128   # dLLM gate/up: whole rounds
-    assert plan(4096, 4096, 12288) == 128   # dLLM down
-    assert plan(4096, 4096, 4096) == 128    # dLLM o-proj
-    assert plan(8192, 4096, 12288) == 128   # whole rounds
-    assert plan(64, 256, 256) in (112, 128)
+    assert plan(9216, 3072, 12288) == 224   # FLUX MLP-down: the 6-bit kernel for many tiles and long K
+    assert plan(4608, 12288, 3072) == 224   # FLUX MLP-up
+    assert plan(4608, 3072, 3072) == 224    # DiT attention projection
+    assert plan(4096, 12288, 4096) == 256   # dLLM gate/up
+    assert plan(4096, 4096, 12288) == 256   # dLLM down
+    assert plan(4096, 8192, 384) == 128     # short K: the int8 kernel
+    assert plan(9216, 3072, 640) == 112     # 112-row tiles fill its last round
+    assert plan(64, 256, 256) == 32         # few tiles
+    for M, N, K in [(1, 64, 64), (77, 12288, 4096), (513, 777, 1024), (2100, 9000, 512), (3003, 5000, 2112),
+                    (9216, 12288, 12288)]:
+        assert plan(M, N, K) == route("w4a4", M, K, N).rows
+    assert plan(1 << 30, 1 << 30, 65536) in (192, 224, 256)  # larger than any launch takes
     L = jq.lib()
     t = ctypes.c_int()
     assert L.jq_gemm_plan(8, 8, 64, 0, ctypes.byref(t)) == jq.JQ_ERR_INVALID_ARG
@@ -327,30 +329,32 @@ def test_gemm_plan():
 
 
 def test_gpu_parity_shapes_cover_both_int8_tile_heights():
-    """The GPU parity cases run the int8 GEMM at both tile heights, with M
-    ragged against each (the height is chosen per shape by the library)."""
+    """The GPU parity cases run the packed engine's int8 kernel at both tile
+    heights, with M ragged against each, and its kernel for few tiles (the
+    library chooses per shape)."""
     from tests.test_gpu_parity import MANY_TILES, RAGGED_LINEARS
 
-    plan = lambda M, N, K: jq.jq_gemm_plan(M, N, K, 256)
-    gemm = {plan(M, N, K) for M, N, K in MANY_TILES}
-    layer = {plan(M, N, K) for M, K, N, _ in RAGGED_LINEARS}
-    assert gemm == {112, 128} and layer == {112, 128}
-    for rows in (112, 128):
-        assert any(plan(M, N, K) == rows and M % rows for M, N, K in MANY_TILES), rows
-        assert any(plan(M, N, K) == rows and M % rows for M, K, N, _ in RAGGED_LINEARS), rows
+    gemm = [(M, route("w4a4", M, K, N)) for M, N, K in MANY_TILES]
+    layer = [(M, route("w4a4", M, K, N)) for M, K, N, _ in RAGGED_LINEARS]
+    for shapes in (gemm, layer):
+        assert {r.rows for _, r in shapes if r.kernel == "tiled"} == {112, 128}
+        assert any(r.kernel == "narrow" for _, r in shapes)
+        for rows in (112, 128):
+            assert any(r.kernel == "tiled" and r.rows == rows and M % rows for M, r in shapes), rows
 
 
 def test_f6_gemm_plan():
-    """The BF6 GEMM's block shape: one 8-wave block per CU where 256-row tiles
-    cover M evenly or K is long, two 4-wave blocks (128-row tiles) otherwise."""
+    """The BF6 GEMM's block shape is that of the kernel which the product takes."""
     plan = lambda M, N, K: jq.jq_f6_gemm_plan(M, N, K, 256)
-    assert plan(4608, 12288, 3072) == (4, 128)    # FLUX MLP-up: 224-row tiles would not cover M evenly
-    assert plan(9216, 3072, 12288) == (8, 224)    # FLUX MLP-down: long K
-    assert plan(4096, 12288, 4096) == (8, 256)    # dLLM gate/up: 256-row tiles fit exactly
-    assert plan(4096, 4096, 12288) == (8, 256)    # dLLM down
-    assert plan(4608, 3072, 3072) == (4, 128)     # DiT attention projection
-    assert plan(4608, 3072, 8192) == (8, 224)     # K above 6144 keeps the 8-wave block
-    assert plan(64, 256, 256) == (4, 128)         # small shapes
+    assert plan(4608, 12288, 3072) == (4, 128)    # FLUX MLP-up: two blocks per CU
+    assert plan(9216, 3072, 12288) == (4, 224)    # FLUX MLP-down
+    assert plan(4096, 12288, 4096) == (4, 256)    # dLLM gate/up: 256-row tiles fit exactly
+    assert plan(4096, 4096, 12288) == (4, 256)    # dLLM down
+    assert plan(4608, 3072, 3072) == (4, 224)     # DiT attention projection
+    assert plan(64, 256, 256) == (4, 32)          # few tiles
+    for M, N, K in [(1, 64, 64), (77, 12288, 4096), (777, 12286, 320), (3003, 5000, 2112), (5400, 2819, 1088)]:
+        r = route("f6", M, K, N)
+        assert plan(M, N, K) == (r.waves, r.rows)
     L = jq.lib()
     w, t = ctypes.c_int(), ctypes.c_int()
     assert L.jq_f6_gemm_plan(8, 8, 64, 0, ctypes.byref(w), ctypes.byref(t)) == jq.JQ_ERR_INVALID_ARG

@@ -1,16 +1,18 @@
 """Seeded random shapes through both engines, every output against the oracle.
 
-Twenty-four shapes drawn from one fixed seed (sixteen with M and N up to
+Thirty-three shapes drawn from two fixed seeds (sixteen with M and N up to
 1500 and K up to 2048; four with M near a multiple of 256 up to 6144, N up
-to 12288 and K up to 512; four with K from 6208 to 8192; bias on or off,
+to 12288 and K up to 512; four with K from 6208 to 8192 and few rows; nine
+with M and N up to 5500 and K up to 3136; bias on or off,
 heavy-tailed activations with outlier columns) cover the tile and edge
-combinations the fixed cases do not name: both tile heights of the int8
-GEMM, the BF6 GEMM's block shapes and tile heights, K tails
+combinations the fixed cases do not name: on the packed engine the few-tile
+kernel, both tile heights of the int8 kernel and all of the 6-bit kernel's; on
+the BF6 engine the few-tile kernel and all of the tiled one's heights; K tails
 (K % 128 == 64), and ragged M and N edges.  Each
 shape runs through jq_w4a4_linear and jq_w4a4_f6_linear (the weight packed
 once and re-encoded for the BF6 engine); both must equal the oracle's bf16
 outputs bit for bit, the quantised activations in the int8 workspace must
-equal the oracle's codes and scales, and the shape's GEMM plans are logged.
+equal the oracle's codes and scales, and the shape's routes are logged.
 Twelve more shapes each do the same for W1.58A4 and for group-wise W4A4
 (G = 64 and 128 alternating, the group sums from the oracle's compiled
 form).
@@ -23,6 +25,7 @@ import pytest
 
 import oracle
 from paper_2609_33601_amd import jq, workloads
+from tests.routes import route
 
 pytestmark = pytest.mark.gpu
 
@@ -35,7 +38,7 @@ def say(*a):
 
 
 def _shapes(seed=20260):
-    """16 small shapes, 4 with many tiles and short K, 4 with K past 6144."""
+    """16 small shapes, 4 with many tiles and short K, 4 with few rows and K past 6144."""
     rng = np.random.default_rng(seed)
     out = []
     for i in range(24):
@@ -50,7 +53,14 @@ def _shapes(seed=20260):
     return out
 
 
-SHAPES = _shapes()
+def _large_shapes(seed=20928):
+    """9 shapes with many tiles and longer K."""
+    rng = np.random.default_rng(seed)
+    return [(int(rng.integers(2000, 5501)), int(rng.integers(1000, 5501)), 64 * int(rng.integers(10, 50)), bool(i % 2),
+             1100 + i) for i in range(9)]
+
+
+SHAPES = _shapes() + _large_shapes()
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -62,21 +72,22 @@ def _gpu():
 
 
 def test_shapes_cover_tile_variety():
-    """The draw includes K tails, both int8 tile heights and both BF6 block shapes."""
+    """The draw includes K tails and every kernel and tile height of both engines."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    heights = {jq.jq_gemm_plan(M, N, K, cus) for M, N, K, _, _ in SHAPES}
-    f6 = {jq.jq_f6_gemm_plan(M, N, K, cus) for M, N, K, _, _ in SHAPES}
+    packed = {route("w4a4", M, K, N, cus=cus) for M, N, K, _, _ in SHAPES}
+    f6 = {route("f6", M, K, N, cus=cus) for M, N, K, _, _ in SHAPES}
     assert any(K % 128 == 64 for _, _, K, _, _ in SHAPES)
-    assert heights == {112, 128}, heights
-    assert {w for w, _ in f6} == {4, 8}, f6
-    say("int8 tile heights drawn:", sorted(heights))
+    rows = lambda routes, kernel: {r.rows for r in routes if r.kernel == kernel}
+    assert rows(packed, "tiled") == {112, 128} and rows(packed, "wide") == {192, 224, 256} and rows(packed, "narrow"), packed
+    assert rows(f6, "tiled") == {128, 160, 192, 224, 256} and rows(f6, "narrow"), f6
+    say("routes drawn:", sorted(packed), sorted(f6))
 
 
 @pytest.mark.parametrize("M,N,K,bias,seed", SHAPES, ids=lambda v: str(v))
 def test_random_shape_both_engines(M, N, K, bias, seed):
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    say(f"{M}x{K}->{N} bias={bias}: int8 tile rows {jq.jq_gemm_plan(M, N, K, cus)}, "
-        f"bf6 (waves, tile rows) {jq.jq_f6_gemm_plan(M, N, K, cus)}")
+    say(f"{M}x{K}->{N} bias={bias}: packed {tuple(route('w4a4', M, K, N, cus=cus))}, "
+        f"bf6 {tuple(route('f6', M, K, N, cus=cus))}")
     x_bits = workloads.activations(M, K, "student_t3", seed, 0.01, 50.0)
     w_bits = workloads.weights(N, K, 0.02, seed + 1)
     b_bits = workloads.bias(N, 0.01, seed + 2) if bias else None
