@@ -419,8 +419,8 @@ jq_status jq_w4a4_f6_linear(const void* x_bf16, int64_t M, int64_t K,
  * quantisation of one input runs inside the bandwidth-bound pass over
  * another instead of as a launch of its own, e.g. the inputs of two linears
  * that do not depend on each other; longer rows get a launch each, on the
- * same stream.  Inputs that all have at most 512 rows share one launch whatever
- * their K.  The quantisation and packing kernels are part of the
+ * same stream.  Inputs that all have at most 512 rows may share one launch
+ * whatever their K.  The quantisation and packing kernels are part of the
  * deployed low-bit operator (appendix FAQ Q7); the paper names the
  * non-GEMM time of a step as what makes speed-ups hard to reach on small
  * models (deployment-summary figure caption, Sec. 1).

@@ -1559,7 +1559,7 @@ GemmRoute f6_group_route(int64_t M, int64_t N, int64_t K, int G, int64_t cus) {
 
 template <int G>
 hipError_t launch_quantize_f6(const uint16_t* x, int64_t M, int64_t K, uint8_t* out, float* scale, hipStream_t st) {
-  if (f6_quantize_few_rows(M)) return launch_quantize_few_f6(x, M, K, G, out, scale, st);
+  if (f6_quantize_few_rows(M, K, G)) return launch_quantize_few_f6(x, M, K, G, out, scale, st);
   const int64_t ksteps = f6_ksteps(K);
   const int64_t groups = 2 * ksteps;
   if (groups <= 512) {
@@ -1587,15 +1587,14 @@ hipError_t launch_quantize_rows_f6(const uint16_t* x, int64_t M, int64_t K, uint
 
 hipError_t launch_quantize_rows_f6_batch(int count, const uint16_t* const* x, const int64_t* M, const int64_t* K,
                                          uint8_t* const* out, float* const* scale, hipStream_t st) {
-  // Inputs of few rows all share a launch of the few-row kernel.  Otherwise
-  // inputs whose rows fit the four-rows-per-block kernel (at most 512 groups)
-  // share one of that, few rows or many (a short input costs less inside
-  // the pass over a long one than as a launch of its own): its waves are the most any of them needs, and NJ the
-  // most sets of groups any of them needs at that wave count.  Longer rows get
-  // a launch of their own, on the same stream.
-  bool few = true;
-  for (int i = 0; i < count; ++i) few = few && f6_quantize_few_rows(M[i]);
-  if (few) return launch_quantize_few_f6_batch(count, x, M, K, out, scale, st);
+  // Inputs of few rows share a launch of the few-row kernel where that is
+  // faster.  Otherwise inputs whose rows fit the four-rows-per-block kernel (at
+  // most 512 groups) share one of that, few rows or many (a short input costs
+  // less inside the pass over a long one than as a launch of its own): its waves
+  // are the most any of them needs, and NJ the most sets of groups any of them
+  // needs at that wave count.  Longer rows get a launch of their own, on the
+  // same stream.
+  if (f6_quantize_few_batch(count, M, K)) return launch_quantize_few_f6_batch(count, x, M, K, out, scale, st);
   Q4Batch b{};
   int waves = 1;
   for (int i = 0; i < count; ++i) {

@@ -1,6 +1,7 @@
 // BF6 quantisers for few rows: the layouts, codes and scales (per token or
-// per group) of quantize_rows4_f6_kernel in f6.hip, byte for byte.  Up to
-// kFewRows rows go here (f6_quantize_few_rows).
+// per group) of quantize_rows4_f6_kernel in f6.hip, byte for byte.
+// f6_quantize_few_rows says which inputs go here, f6_quantize_few_batch which
+// batches.
 //
 // What bounds few rows.  Four rows per block of 32 codes per lane leave 64
 // rows to 16 blocks, on the two XCDs their bands belong to, and each lane
@@ -31,6 +32,7 @@ using namespace f6_detail;
 typedef unsigned v4u32 __attribute__((ext_vector_type(4)));
 
 constexpr int64_t kFewRows = 512;
+constexpr int64_t kFourRowsMaxK = 16384;  // the four-row kernel's longest row
 
 // The lane's value of v at lane perm[l % 4] of its quad (CTRL as in quad_perm).
 template <int CTRL>
@@ -208,6 +210,7 @@ hipError_t launch_few(const uint16_t* x, int64_t M, int64_t K, uint8_t* out, flo
   else if (nc <= 2) JQ_FEW(2);
   else if (nc <= 3) JQ_FEW(3);
   else if (nc <= 4) JQ_FEW(4);
+  else if (nc <= 6) JQ_FEW(6);  // (as 8, loads of nothing made 96 x 49152 13.9 us, against 13.4 by the one-row kernel)
   else JQ_FEW(8);
 #undef JQ_FEW
   return hipGetLastError();
@@ -215,7 +218,52 @@ hipError_t launch_few(const uint16_t* x, int64_t M, int64_t K, uint8_t* out, flo
 
 }  // namespace
 
-bool f6_quantize_few_rows(int64_t M) { return M <= kFewRows; }
+// Rows of up to 16384 codes: against the four-row kernel this one is 15 to 60%
+// faster up to 512 rows (G 0, 64 and 128, K 64..16384); from 1024 rows on it is
+// slower.  Longer rows go to the one-row kernel of f6.hip otherwise, which reads
+// them with 512 threads instead of 1024: per token it is faster or level for
+// fewer than 32 rows (2 x 49152 8.7 against 9.8 us) and for more than 160 (384 x
+// 65536 28.6 against 38.4), between them 2 to 35% slower; with group scales,
+// which need no maximum over the row, it is faster from 16 rows on (256 x 20480
+// 7.5 against 10.1, 512 x 20480 11.5 against 17.3) and up to 4 rows slower by 5
+// to 40%.
+bool f6_quantize_few_rows(int64_t M, int64_t K, int G) {
+  if (K <= kFourRowsMaxK) return M <= kFewRows;
+  return G == 0 ? M >= 32 && M <= 160 : M <= 4;
+}
+
+// Whether a batch takes one launch of the few-row kernel, by estimated times in
+// ns.  The few-row kernel: 2300, 1 per 900 codes and half of one per row, at
+// least the walk along the longest row.  Otherwise the inputs of up to 16384
+// codes a row share a launch of the four-row kernel, whose blocks start every
+// input on XCD 0: the walk (0.6 per code of the longest row) and the codes of
+// that XCD (x 8, at 1300) overlap in part; and longer rows take a launch of
+// their own each.  Fitted to 180 batches and 110 single inputs (1..8 inputs, M
+// 1..512, K 64..16384, some to 65536): 0.1% off the better of the two on
+// average.  (8 x 128 x 4096 11.1 us by the four-row kernel, 8.7 by this one; 4 x
+// 512 x 4096 10.0 and 14.5.)
+bool f6_quantize_few_batch(int count, const int64_t* M, const int64_t* K) {
+  int64_t rows = 0, codes = 0, longest = 0, four_longest = 0, xcd_codes = 0, apart = 0;
+  for (int i = 0; i < count; ++i) {
+    if (M[i] > kFewRows) return false;
+    rows += M[i];
+    codes += M[i] * K[i];
+    longest = std::max(longest, K[i]);
+    if (K[i] <= kFourRowsMaxK) {
+      four_longest = std::max(four_longest, K[i]);
+      xcd_codes += (M[i] < 32 ? M[i] : (M[i] + 255) / 256 * 32) * K[i];
+    } else {
+      apart += std::max(3000 + K[i] * 1000 / 8192, 3000 + M[i] * K[i] / 1000);
+    }
+  }
+  const int64_t few = std::max(2500 + longest * 1000 / 8192, 2300 + codes / 900 + rows / 2);
+  int64_t other = apart;
+  if (four_longest > 0) {
+    const int64_t walk = 3400 + four_longest * 6 / 10, load = 1000 + 8 * xcd_codes / 1300;
+    other += std::max(walk, load) + std::min(walk, load) * 3 / 10;
+  }
+  return few <= other;
+}
 
 hipError_t launch_quantize_few_f6(const uint16_t* x, int64_t M, int64_t K, int G, uint8_t* out, float* scale,
                                   hipStream_t st) {

@@ -555,4 +555,10 @@ int jq_internal_route(int kind, int64_t M, int64_t N, int64_t K, int G, int cus,
   return 0;
 }
 
+int jq_internal_quantize_few(int64_t M, int64_t K, int G) { return jq::f6_quantize_few_rows(M, K, G); }
+
+int jq_internal_quantize_few_batch(int count, const int64_t* M, const int64_t* K) {
+  return jq::f6_quantize_few_batch(count, M, K);
+}
+
 }  // extern "C"

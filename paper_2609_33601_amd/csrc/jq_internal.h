@@ -114,10 +114,11 @@ hipError_t launch_quantize_rows_f6(const uint16_t* x, int64_t M, int64_t K, uint
 hipError_t launch_quantize_rows_f6_batch(int count, const uint16_t* const* x, const int64_t* M, const int64_t* K,
                                          uint8_t* const* out, float* const* scale, hipStream_t st);
 
-// The BF6 quantisers' kernel for few rows (G = 0: per token): whether an input
-// of M rows goes there, its launch, and its batched form (every input of few
-// rows, count <= 8).
-bool f6_quantize_few_rows(int64_t M);
+// The BF6 quantisers' kernel for few rows (G = 0: per token): whether an M x K
+// input goes there, and a batch as a whole; its launch, and its batched form
+// (inputs of up to 512 rows, count <= 8).
+bool f6_quantize_few_rows(int64_t M, int64_t K, int G);
+bool f6_quantize_few_batch(int count, const int64_t* M, const int64_t* K);
 hipError_t launch_quantize_few_f6(const uint16_t* x, int64_t M, int64_t K, int G, uint8_t* out, float* scale,
                                   hipStream_t st);
 hipError_t launch_quantize_few_f6_batch(int count, const uint16_t* const* x, const int64_t* M, const int64_t* K,
@@ -155,5 +156,8 @@ hipError_t noalloc_scratch(void** ptr);
 // 1 for a kind that does not exist.  Sizes are not checked.
 enum { JQ_ROUTE_W4A4 = 0, JQ_ROUTE_W158A4 = 1, JQ_ROUTE_W4A4_F6 = 2, JQ_ROUTE_W4A4G_F6 = 3 };
 extern "C" int jq_internal_route(int kind, int64_t M, int64_t N, int64_t K, int G, int cus, int out[4]);
+// Whether the BF6 quantisers take the few-row kernel: for one input, for a batch.
+extern "C" int jq_internal_quantize_few(int64_t M, int64_t K, int G);
+extern "C" int jq_internal_quantize_few_batch(int count, const int64_t* M, const int64_t* K);
 
 #endif  // JQ_INTERNAL_H

@@ -25,3 +25,19 @@ def route(kind, M, K, N, G=0, cus=256):
     out = (ctypes.c_int * 4)()
     assert fn(KINDS[kind], M, N, K, G, cus, ctypes.byref(out)) == 0, kind
     return Route(KERNELS[out[0]], out[1], out[2], out[3])
+
+
+def few_rows(M, K, G=0):
+    """Whether the BF6 quantiser takes the few-row kernel for an M x K input."""
+    fn = jq.lib().jq_internal_quantize_few
+    fn.argtypes, fn.restype = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int], ctypes.c_int
+    return bool(fn(M, K, G))
+
+
+def few_rows_batch(shapes):
+    """Whether the batched BF6 quantiser takes one launch of the few-row kernel for M x K inputs."""
+    fn = jq.lib().jq_internal_quantize_few_batch
+    n = len(shapes)
+    fn.argtypes, fn.restype = [ctypes.c_int] + [ctypes.POINTER(ctypes.c_int64 * n)] * 2, ctypes.c_int
+    return bool(fn(n, ctypes.byref((ctypes.c_int64 * n)(*[m for m, _ in shapes])),
+                   ctypes.byref((ctypes.c_int64 * n)(*[k for _, k in shapes]))))

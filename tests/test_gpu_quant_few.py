@@ -1,19 +1,22 @@
 """The BF6 quantisers' few-row kernel against the four-row and the long-row kernels.
 
-An input of up to 512 rows takes the few-row kernel, one of more rows the
+An input of up to 512 rows of up to 16384 codes takes the few-row kernel (of
+longer rows, fewer: see f6_quantize_few_rows), one of more rows the
 others, whose codes and scales the oracle tests pin.  The first rows of a
 longer input must therefore come out byte for byte as they do alone, padding
 included: operand bytes and scale bits, per token and per group, for row
 lengths at the kernel's edges (a part of a wave, one chunk per thread, a K
 tail, the longest register-resident row, rows of several chunks per thread),
 with rows that take its special paths (zeros, exact ties, a reciprocal that
-overflows, infinities and NaN).  The batched form must equal single calls.
+overflows, infinities and NaN).  The batched form must equal single calls, on
+both of its kernels.
 """
 
 import numpy as np
 import pytest
 
 from paper_2609_33601_amd import jq, workloads
+from tests.routes import few_rows, few_rows_batch
 
 pytestmark = pytest.mark.gpu
 
@@ -35,14 +38,16 @@ def _rows(M, K, seed):
 
 @pytest.mark.parametrize("G", [0, 64, 128])
 @pytest.mark.parametrize("M,K", [(1, 64), (2, 128), (33, 192), (512, 256), (7, 3072), (96, 4096), (64, 4160),
-                                 (31, 12288), (5, 16384), (3, 16448), (6, 20480), (2, 32832), (4, 65536)],
+                                 (31, 12288), (5, 16384), (3, 16448), (6, 20480), (2, 32832), (4, 65536),
+                                 (33, 16448), (40, 20480), (4, 20480), (4, 49152), (32, 32832), (48, 49152), (160, 65536)],
                          ids=lambda v: str(v))
 def test_few_rows_equal_many(M, K, G):
     if not torch.cuda.is_available():
         pytest.fail("no GPU visible")
     if G and K % G:
         pytest.skip("not a multiple of the group")
-    print(f"[gpu-quant-few] {M}x{K} G={G}", flush=True)
+    print(f"[gpu-quant-few] {M}x{K} G={G} few={few_rows(M, K, G)}", flush=True)
+    assert not few_rows(544, K, G)
     x = torch.zeros((544, K), dtype=torch.bfloat16, device="cuda")
     x[:M] = jq.bf16_tensor(_rows(M, K, M + K), "cuda")
     f = (lambda t: jq.jq_quantize_act_group_f6(t, G)) if G else jq.jq_quantize_act_f6
@@ -63,9 +68,9 @@ def test_few_rows_equal_many(M, K, G):
 
 
 @pytest.mark.parametrize("shapes", [[(1, 64)], [(64, 4096), (3, 12288), (40, 256)], [(5, 20480), (512, 192), (1, 65536)],
-                                    [(9, 3072), (700, 128)]], ids=str)
+                                    [(9, 3072), (700, 128)], [(512, 4096), (512, 4096), (300, 1024), (512, 12288)]], ids=str)
 def test_few_rows_batch(shapes):
-    print("[gpu-quant-few] batch", shapes, flush=True)
+    print("[gpu-quant-few] batch", shapes, "few", few_rows_batch(shapes), flush=True)
     xs = [jq.bf16_tensor(_rows(M, K, i), "cuda") for i, (M, K) in enumerate(shapes)]
     qs, ss = jq.jq_quantize_act_f6_batch(xs)
     for x, q, s in zip(xs, qs, ss):

@@ -1,0 +1,58 @@
+"""Which kernel the library's rules give a call (host only).
+
+The GPU tests of a kernel name shapes that are meant to reach it.  The rules are
+fitted to measured times and may be fitted again, so that a shape changes over
+with every test still passing: here each list is held to the kernels and tiles
+that it is meant for, at the 256 CUs of an MI355X.
+"""
+
+import os
+
+import pytest
+
+from paper_2609_33601_amd import jq
+from tests.routes import few_rows, few_rows_batch
+
+pytestmark = pytest.mark.skipif(not os.path.exists(jq.LIB_PATH),
+                                reason="libjq.so not built (run __graft_entry__.build())")
+
+
+def test_few_row_quantiser_only_where_it_is_faster():
+    for G in (0, 64, 128):
+        for K in (128, 3072, 12288, 16384):
+            assert few_rows(1, K, G) and few_rows(512, K, G) and not few_rows(513, K, G)
+    # longer rows: measured slower than the one-row kernel here
+    for K in (20480, 49152, 65536):
+        for M in (1, 192, 384, 512):
+            assert not few_rows(M, K), (M, K)
+        for M in (16, 64, 128, 256, 512):
+            assert not few_rows(M, K, 64) and not few_rows(M, K, 128), (M, K)
+        assert few_rows(64, K) and few_rows(2, K, 64) and few_rows(2, K, 128)
+
+
+@pytest.mark.parametrize("shapes", [[(512, 4096)] * 2, [(512, 4096)] * 4, [(512, 16384)] * 2, [(256, 12288)] * 4,
+                                    [(512, 3072)] * 8, [(256, 3072)] * 4, [(600, 64), (1, 64)]], ids=str)
+def test_batches_that_the_four_row_kernel_does_faster(shapes):
+    assert not few_rows_batch(shapes)
+
+
+@pytest.mark.parametrize("shapes", [[(64, 4096), (64, 12288)], [(128, 4096)] * 8, [(384, 8192)] * 2, [(1, 64)],
+                                    [(512, 256)] * 4, [(29, 8832), (28, 37568), (2, 384)]], ids=str)
+def test_batches_that_the_few_row_kernel_does_faster(shapes):
+    assert few_rows_batch(shapes)
+
+
+def test_quantiser_shapes_reach_the_few_row_kernel():
+    from tests.test_gpu_quant_few import test_few_rows_batch, test_few_rows_equal_many
+
+    shapes = _params(test_few_rows_equal_many, "M,K")
+    for G in (0, 64, 128):
+        lengths = {K for M, K in shapes if (not G or K % G == 0) and few_rows(M, K, G)}
+        assert min(lengths) <= 128 and max(lengths) == 65536 and any(16384 < K < 65536 for K in lengths), (G, lengths)
+    batches = _params(test_few_rows_batch, "shapes")
+    assert {few_rows_batch(b) for b in batches if max(M for M, _ in b) <= 512} == {False, True}
+
+
+def _params(test, names):
+    """The values that a test is parametrised with over `names`."""
+    return next(m.args[1] for m in test.pytestmark if m.name == "parametrize" and m.args[0] == names)
