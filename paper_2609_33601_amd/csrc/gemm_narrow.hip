@@ -222,8 +222,8 @@ constexpr NarrowTile kTiles[] = {{1, 1, 4, 3600}, {2, 2, 2, 4700}, {2, 3, 2, 630
 // per 128 codes for a block alone on its CU, 1550 for two, and never with
 // more.  Fitted to 286 measured shapes (M 1..2048, K 256..12288, N
 // 256..12288); a call changes over only where the estimate says at least 10%
-// less.
-int gemm_narrow_tile(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus) {
+// less; *ns is the estimate of the tile.
+int gemm_narrow_tile(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus, int64_t* ns) {
   const bool tern = wf == WeightFormat::kTernary;
   const int64_t units = (K + 127) / 128, mb = (M + 31) / 32, nb = (N + 31) / 32;
   const int64_t tiled_n = ((M + 127) / 128 * ((N + 255) / 256) + cus - 1) / cus;
@@ -236,9 +236,10 @@ int gemm_narrow_tile(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t c
     ++i;
     const int64_t n = ((mb + t.mb - 1) / t.mb * ((nb + t.nb - 1) / t.nb) + cus - 1) / cus;
     const int64_t bytes = 2048 * t.mb + (tern ? 1024 : 2048) * t.nb;  // of a tile, per 128 codes
-    const int64_t ns = n * units * bytes / 42 + (n + t.per_cu - 1) / t.per_cu * (t.fixed + (tern ? 900 : 0));
-    if (ns < best_ns) best = i, best_ns = ns;
+    const int64_t t_ns = n * units * bytes / 42 + (n + t.per_cu - 1) / t.per_cu * (t.fixed + (tern ? 900 : 0));
+    if (t_ns < best_ns) best = i, best_ns = t_ns;
   }
+  *ns = best_ns;
   return best;
 }
 

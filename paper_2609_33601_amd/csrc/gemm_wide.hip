@@ -67,6 +67,7 @@ typedef unsigned v2u32 __attribute__((ext_vector_type(2)));
 
 constexpr int kBN = 256;        // tile columns
 constexpr int kWaves = 4;
+constexpr int kStep = 256;      // codes of K per step
 constexpr int kFrag = 1536;     // one 32-row x 64-code fragment
 constexpr int kLgkm0 = 0xC07F;  // lgkmcnt(0), other counters untouched
 
@@ -123,12 +124,12 @@ __global__ __launch_bounds__(64 * kWaves, 1) void w4a4_wide_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int li = lane & 31, lh = lane >> 5;
   const uint32_t row_bytes = K / 2, wrow_bytes = kTern ? K / 4 : K / 2;
-  const int T = (K + 255) / 256;  // steps per tile
+  const int T = (K + kStep - 1) / kStep;  // steps per tile, two or more
   const int last = T - 1;
 
   // As the int8 kernel's: virtual block ids of a grid of 8 * ceil(tiles / 8) in
-  // the XCD-aware order.  The launch gives every block a single tile when a
-  // tile has one step, since the loads run two steps ahead.
+  // the XCD-aware order.  (The loads run two steps ahead, at most into the next
+  // tile: a tile has two steps or more.)
   int ntiles = 0;
   {
     const int vmax = (tiles_m * tiles_n + kNumXcd - 1) / kNumXcd * kNumXcd;
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(64 * kWaves, 1) void w4a4_wide_kernel(
       v += __shfl_xor(v, 1, 64);
       v += __shfl_xor(v, 2, 64);
       v += __shfl_xor(v, 4, 64);
-      if (xc == 0) sc_cx[32 * j + xr] = static_cast<float>(oW * v + oX * oW * 256 * T);
+      if (xc == 0) sc_cx[32 * j + xr] = static_cast<float>(oW * v + oX * oW * kStep * T);
       rs[j] = 0;
     }
   };
@@ -269,13 +270,13 @@ __global__ __launch_bounds__(64 * kWaves, 1) void w4a4_wide_kernel(
   for (int j = 0; j < NFM; ++j) {
     conv_x(0, j, C0{});
     conv_x(0, j, C1{});
-    load_x(T > 1 ? ct.x : xt.x, k1, j);
+    load_x(ct.x, k1, j);
   }
   static_for<2>([&](auto F) __attribute__((always_inline)) {
     constexpr int f = decltype(F)::value;
     conv_w(F, C0{}, C0{}, lead[f]);
     conv_w(F, C0{}, C1{}, lead[f]);
-    if constexpr (!kTern) load_w(T > 1 ? ct.w : xt.w, k1, f, 0);
+    if constexpr (!kTern) load_w(ct.w, k1, f, 0);
   });
   __builtin_amdgcn_s_waitcnt(kLgkm0);
   __builtin_amdgcn_s_barrier();
@@ -481,12 +482,6 @@ __global__ __launch_bounds__(64 * kWaves, 1) void w4a4_wide_kernel(
       const uint32_t z = s0;
       s0 = s1, s1 = z;
     }
-    if (T == 1) {
-      // the scales were stored in this very step
-      __builtin_amdgcn_s_waitcnt(kLgkm0);
-      __builtin_amdgcn_s_barrier();
-      asm volatile("" ::: "memory");
-    }
     epilogue(ct.m0, ct.n0);
     ct = xt;
     if (ti + 2 < ntiles) xt = tile_at(ti + 2);
@@ -496,8 +491,11 @@ __global__ __launch_bounds__(64 * kWaves, 1) void w4a4_wide_kernel(
 }  // namespace
 
 // The tile height in bands of 32 rows (6, 7 or 8) with which a product takes
-// this kernel, or 0 for the int8 kernel.  Both are estimated in ns for the XCD
-// with most tiles, on its share of `cus`:
+// this kernel, and the estimate it was picked by, or 0 for the int8 kernel.  A K
+// of one step goes to the int8 kernel: here nothing runs under its loads (1147 x
+// 192 -> 8960 13.4 us against 10.0, 1183 x 256 -> 8192 13.0 against 11.5; of 20
+// such shapes ten were slower here by more than 2%, seven faster).  Both are
+// estimated in ns for the XCD with most tiles, on its share of `cus`:
 //   this kernel: its rounds, each 185 b + 299 per 256 codes (ternary 97 b + 936)
 //   and 1545 b (1657 b) for the epilogue;
 //   the int8 kernel: its rounds of two 128- or 112-row tiles per CU (a last
@@ -506,7 +504,8 @@ __global__ __launch_bounds__(64 * kWaves, 1) void w4a4_wide_kernel(
 // 1024..12288).  The switch is where the estimate says 10% less: of 66 int4
 // shapes that take it none is slower, the whole set is 10% faster on average
 // (ternary 6.5%), and the best of all tiles would give 1.4% more.
-int gemm_wide_bands(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus) {
+int gemm_wide_bands(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus, int64_t* ns) {
+  if (K <= kStep) return 0;
   const bool tern = wf == WeightFormat::kTernary;
   const int64_t tiles_n = (N + kBN - 1) / kBN, xcd_cus = std::max<int64_t>(1, cus / kNumXcd);
   auto per_xcd = [&](int64_t rows) { return ((M + rows - 1) / rows * tiles_n + kNumXcd - 1) / kNumXcd; };
@@ -515,17 +514,18 @@ int gemm_wide_bands(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cu
     const int64_t n = per_xcd(rows), rest = n % (2 * xcd_cus);
     const int64_t rounds = 100 * (n / (2 * xcd_cus)) + (rest == 0 ? 0 : rest <= xcd_cus ? 67 : 100);
     // 128 bits: a plan may be asked for sizes that no launch accepts
-    const int64_t ns = static_cast<int64_t>(static_cast<__int128>(rounds) * (rows == 128 ? 100 : 93) *
-                                            (1190 * ((K + 127) / 128) + 10500) / 10000);
-    if (best_ns < 0 || ns < best_ns) best_ns = ns;
+    const int64_t t = static_cast<int64_t>(static_cast<__int128>(rounds) * (rows == 128 ? 100 : 93) *
+                                           (1190 * ((K + 127) / 128) + 10500) / 10000);
+    if (best_ns < 0 || t < best_ns) best_ns = t;
   }
   best_ns = best_ns * 90 / 100;
   int best = 0;
   for (int b = 8; b >= 6; --b) {
-    const int64_t ns = (per_xcd(32 * b) + xcd_cus - 1) / xcd_cus *
-                       ((K + 255) / 256 * (tern ? 97 * b + 936 : 185 * b + 299) + (tern ? 1657 : 1545) * b);
-    if (ns < best_ns) best = b, best_ns = ns;
+    const int64_t t = (per_xcd(32 * b) + xcd_cus - 1) / xcd_cus *
+                      ((K + kStep - 1) / kStep * (tern ? 97 * b + 936 : 185 * b + 299) + (tern ? 1657 : 1545) * b);
+    if (t < best_ns) best = b, best_ns = t;
   }
+  *ns = best_ns;
   return best;
 }
 
@@ -535,9 +535,9 @@ hipError_t launch_gemm_wide(int bands, Epilogue epi, const uint8_t* qx, const fl
   const int tiles_m = static_cast<int>((M + 32 * bands - 1) / (32 * bands));
   const int tiles_n = static_cast<int>((N + kBN - 1) / kBN);
   const int64_t per_xcd = (static_cast<int64_t>(tiles_m) * tiles_n + kNumXcd - 1) / kNumXcd;
-  const int blocks = static_cast<int>(K <= 256 ? per_xcd * kNumXcd : std::min<int64_t>(per_xcd * kNumXcd, cus));
+  const int blocks = static_cast<int>(std::min<int64_t>(per_xcd * kNumXcd, cus));
   const int Mi = static_cast<int>(M), Ki = static_cast<int>(K), Ni = static_cast<int>(N);
-  const bool tail = K % 256 != 0;
+  const bool tail = K % kStep != 0;
 #define JQ_W(W, NF, E, B, T)                                                                                      \
   hipLaunchKernelGGL((w4a4_wide_kernel<W, NF, E, B, T>), dim3(blocks), dim3(64 * kWaves), 0, st, qx, sx, Mi, Ki, qw, \
                      sw, Ni, bias, out, tiles_m, tiles_n, blocks)

@@ -59,18 +59,18 @@ hipError_t device_route_cus(int64_t* cus);
 int gemm_tile_rows(int64_t M, int64_t N, int64_t slots);
 
 // Its kernel for products with few output tiles: which of its tiles an M x K
-// by K x N product on `cus` CUs takes (0: none, it goes to the tiled kernel),
-// and its launch.
-int gemm_narrow_tile(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus);
+// by K x N product on `cus` CUs takes instead of the tiled kernel (0: none) and
+// its estimated time, and its launch.
+int gemm_narrow_tile(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus, int64_t* ns);
 void gemm_narrow_shape(int tile, int* rows, int* cols);
 hipError_t launch_gemm_narrow(int tile, Epilogue epi, const uint8_t* qx, const float* sx, int64_t M, int64_t K,
                               const uint8_t* qw, const float* sw, int64_t N, const uint16_t* bias, void* out,
                               hipStream_t st, WeightFormat wf);
 
 // The same on the 6-bit matrix cores, operands converted inside the kernel:
-// tile height in bands of 32 rows for a product that takes it (0: none), and
-// its launch.
-int gemm_wide_bands(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus);
+// tile height in bands of 32 rows for a product that is faster on it than on the
+// int8 kernel (0: none) and its estimated time, and its launch (K > 256).
+int gemm_wide_bands(int64_t M, int64_t N, int64_t K, WeightFormat wf, int64_t cus, int64_t* ns);
 hipError_t launch_gemm_wide(int bands, Epilogue epi, const uint8_t* qx, const float* sx, int64_t M, int64_t K,
                             const uint8_t* qw, const float* sw, int64_t N, const uint16_t* bias, void* out, int64_t cus,
                             hipStream_t st, WeightFormat wf);
