@@ -71,6 +71,9 @@ constexpr int kStep = 256;      // codes of K per step
 constexpr int kFrag = 1536;     // one 32-row x 64-code fragment
 constexpr int kLgkm0 = 0xC07F;  // lgkmcnt(0), other counters untouched
 
+// Every sum of products of offset codes (at most 15 * 15) is exact in fp32.
+static_assert(15 * 15 * kMaxK < (int64_t(1) << 24), "a sum of products would not fit fp32");
+
 template <typename F, int... I>
 __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
   (f(std::integral_constant<int, I>{}), ...);

@@ -87,3 +87,28 @@ def test_wide_extreme_codes():
     a = jq.jq_w4a4_gemm_i32(pack(mc), pack(nc))
     torch.cuda.synchronize()
     assert torch.equal(a.long(), mc[:, None] * nc[None, :] * K), "accumulators differ"
+
+
+def test_wide_odd_sums_near_the_bound():
+    """The longest K with codes close to the largest: sums of the offset codes' products between
+    2^23 and 225 * 65536 with their low bits in use, where fp32 has no bit to spare."""
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible: the parity tests need an MI355X")
+    M, K, N = 4096, 65536, 4096
+    print(f"[gpu-gemm-wide] near the bound {M}x{K}->{N}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    # row r draws from 7 - r % 4 .. 7
+    draw = lambda R: 7 - (torch.rand((R, K), generator=g, device="cuda")
+                          * (1 + torch.arange(R, device="cuda") % 4)[:, None]).to(torch.int8)
+    pack = lambda c: (c[:, 0::2] | (c[:, 1::2] << 4)).to(torch.uint8)
+    cx, cw = draw(M), draw(N)
+    a = jq.jq_w4a4_gemm_i32(pack(cx), pack(cw))
+    torch.cuda.synchronize()
+    sx, sw = cx.sum(1, dtype=torch.int64), cw.sum(1, dtype=torch.int64)
+    ref = torch.zeros((M, N), dtype=torch.float64, device="cuda")
+    for k in range(0, K, 8192):
+        ref += cx[:, k:k + 8192].double() @ cw[:, k:k + 8192].double().t().contiguous()
+    ref = ref.long()
+    offset = ref + 8 * (sx[:, None] + sw[None, :]) + 64 * K  # what the matrix cores add up
+    assert int(offset.min()) > 2 ** 23 and int(offset.max()) > 14.7e6 and len((offset % 64).unique()) == 64
+    assert torch.equal(a.long(), ref), "accumulators differ"
