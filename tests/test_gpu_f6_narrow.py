@@ -5,8 +5,9 @@ waves split K in units of 128 codes and it loads two units ahead.  The shapes
 sit on the edges of these: one row or column, one past a band, a tile's last
 band or column absent, N not a multiple of 4 (element-wise stores), K of one
 unit, of half a unit, of less than a unit per wave, of an odd number of units
-per wave.  They cover each of its tiles (N and K decide which), and three
-ragged shapes just past the line, on the tiled kernel's both block shapes.
+per wave.  They cover each of its tiles (the rules' estimates decide which), and
+three ragged shapes just past the line, on the tiled kernel with one block per
+CU and with two.
 Accumulators and outputs must equal the oracle's bit for bit: the contraction
 is exact in any order and the epilogue's rounding steps are the oracle's.
 """
@@ -24,8 +25,8 @@ torch = pytest.importorskip("torch")
 # M, K, N, bias
 SHAPES = [
     (1, 64, 1, True), (32, 64, 30, False), (31, 192, 33, True), (65, 1024, 999, True), (33, 4096, 4095, False),
-    (1, 12288, 4, False),                                              # 1x1
-    (96, 12288, 4097, True), (3, 3072, 12288, False),                  # 1x2
+    (1, 12288, 4, False), (3, 3072, 12288, False),                     # 1x1
+    (96, 12288, 4097, True),                                           # 1x2
     (300, 12288, 3000, True), (64, 4096, 12288, False), (40, 4160, 12287, True),  # 2x2
     (97, 3072, 12285, True), (512, 3072, 3072, False),                 # 2x3
     (1500, 6272, 5000, True), (2300, 6208, 3001, True), (777, 320, 12286, True),  # the tiled kernel

@@ -2,10 +2,10 @@
 
 Its tile is 32 x 32, its four or eight waves take one unit of 128 codes each
 per round, and every output's group terms are added in k order.  The shapes
-sit on the edges: one row or column, one past a band, odd N, K of one group,
-of one unit, of fewer units than waves, of a last round that is not full and
-(G = 64) ends in half a unit; with either number of waves, and just past the
-line on the tiled kernel (ragged).  Sums and outputs must equal the oracle's
+sit on the edges: one row, a few columns, one past a band, odd N, K of fewer
+units than waves, of a last round that is not full and (G = 64) ends in half a
+unit; with either number of waves, and just past the line on the tiled kernel
+(ragged; K of one group, of one unit).  Sums and outputs must equal the oracle's
 bit for bit: every fp32 step of the layer is rounded on its own, in a fixed
 order.  A row of zeros, whose scales are zero, stays the bias.
 """

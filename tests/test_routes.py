@@ -61,6 +61,47 @@ def test_few_tile_kernel_gives_way_to_the_six_bit_one(kind, M, K, N):
     assert route(kind, M, K, N).kernel == "wide"
 
 
+def test_packed_gemm_shapes_reach_their_kernel():
+    from tests import test_gpu_gemm_narrow, test_gpu_gemm_tiled, test_gpu_gemm_wide
+
+    for kind, tiled, wide in (("w4a4", test_gpu_gemm_tiled.INT4, test_gpu_gemm_wide.INT4),
+                              ("w158a4", test_gpu_gemm_tiled.TERNARY, test_gpu_gemm_wide.TERNARY)):
+        for height, M, K, N in tiled:
+            assert route(kind, M, K, N)[::2] == ("tiled", height), (kind, M, K, N)
+        for h in (112, 128):
+            assert {K % 128 for height, _, K, _ in tiled if height == h} == {0, 64}
+        for bands, M, K, N, _ in wide:
+            # int4 shapes of one step are the int8 kernel's
+            assert route(kind, M, K, N)[::2] == (("wide", 32 * bands) if K > 256 else ("tiled", 112)), (kind, M, K, N)
+        narrow = [route(kind, M, K, N) for M, K, N, _ in test_gpu_gemm_narrow.SHAPES]
+        assert [r.kernel for r in narrow] == ["narrow"] * (len(narrow) - 2) + ["tiled"] * 2
+        assert {(r.rows, r.cols) for r in narrow[:-2]} == {(32, 32), (64, 64), (64, 96)}
+    # the extreme codes at the longest K
+    assert route("w4a4", 4096, 65536, 4096).kernel == "wide"
+
+
+def test_bf6_gemm_shapes_reach_their_kernel():
+    from tests import test_gpu_f6_narrow, test_gpu_f6_tiles
+
+    for bands, M, K, N, _ in test_gpu_f6_tiles.SHAPES:
+        assert route("f6", M, K, N)[::2] == ("tiled", 32 * bands), (M, K, N)
+    got = [route("f6", M, K, N) for M, K, N, _ in test_gpu_f6_narrow.SHAPES]
+    want = [(32, 32)] * 7 + [(32, 64)] + [(64, 64)] * 3 + [(64, 96)] * 2
+    assert [(r.rows, r.cols) for r in got[:-3]] == want and {r.kernel for r in got[:-3]} == {"narrow"}
+    assert {r.kernel for r in got[-3:]} == {"tiled"} and {r.rows == 128 for r in got[-3:]} == {False, True}
+
+
+def test_group_gemm_shapes_reach_their_kernel():
+    from tests import test_gpu_group_narrow, test_gpu_group_tiles
+
+    for M, K, N, G, _ in test_gpu_group_tiles.SHAPES:
+        assert route("group_f6", M, K, N, G).kernel == "tiled", (M, K, N, G)
+    got = [(K, G, route("group_f6", M, K, N, G)) for M, K, N, G, _ in test_gpu_group_narrow.SHAPES]
+    assert {(G, r.waves) for _, G, r in got if r.kernel == "narrow"} == {(64, 4), (64, 8), (128, 4), (128, 8)}
+    assert any(K % 128 == 64 and r.kernel == "narrow" and r.waves == w for K, _, r in got for w in (4, 8))
+    assert sum(r.kernel == "tiled" for _, _, r in got) >= 4
+
+
 def test_one_step_of_k_stays_off_the_six_bit_packed_kernel():
     # its loads run two steps of 256 codes ahead, at most into the block's next tile
     for kind in ("w4a4", "w158a4"):
