@@ -121,8 +121,12 @@ def _torch():
 def _stream_ptr(stream):
     if stream is not None:
         return stream.cuda_stream
-    c = _torch()._C
-    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    torch = _torch()
+    try:
+        c = torch._C
+        return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    except AttributeError:  # private names, which another torch may not have
+        return torch.cuda.current_stream().cuda_stream
 
 
 def _dev(t, dtype, shape, name):

@@ -360,3 +360,16 @@ def test_f6_gemm_plan():
     assert L.jq_f6_gemm_plan(8, 8, 64, 0, ctypes.byref(w), ctypes.byref(t)) == jq.JQ_ERR_INVALID_ARG
     assert L.jq_f6_gemm_plan(8, 8, 64, 256, None, ctypes.byref(t)) == jq.JQ_ERR_INVALID_ARG
     assert L.jq_f6_gemm_plan(8, 8, 96, 256, ctypes.byref(w), ctypes.byref(t)) == jq.JQ_ERR_UNSUPPORTED_SHAPE
+
+
+def test_stream_without_torchs_private_names(monkeypatch):
+    """The current stream is found by the public call where torch lacks the cheaper private ones."""
+    from types import SimpleNamespace as NS
+
+    cuda = NS(current_stream=lambda: NS(cuda_stream=0x1234))
+    monkeypatch.setattr(jq, "_torch_module", NS(_C=NS(), cuda=cuda))
+    assert jq._stream_ptr(None) == 0x1234
+    raw = NS(_cuda_getDevice=lambda: 3, _cuda_getCurrentRawStream=lambda dev: 0x5670 + dev)
+    monkeypatch.setattr(jq, "_torch_module", NS(_C=raw, cuda=cuda))
+    assert jq._stream_ptr(None) == 0x5673
+    assert jq._stream_ptr(NS(cuda_stream=7)) == 7
