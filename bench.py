@@ -12,8 +12,10 @@ seeded synthetic tensors already resident in HBM.
 The library computes the layer on two engines with bit-identical results:
   * bf6:  codes carried as BF6 on gfx950's 6-bit MFMA (fp32 accumulation,
           exact for integer codes), the faster one, timed as `value`;
-  * int8: packed int4 codes widened to int8 for the int8 MFMA (int32
-          accumulation), reported beside it under `engines`.
+  * int8: packed int4 codes, widened inside the GEMM: to E2M3 for the 6-bit
+          MFMA (exact fp32 sums) for large products, both FLUX linears among
+          them, to int8 for the int8 MFMA (int32 sums) for the others;
+          reported beside it under `engines`.
 
 Timing protocol.  The first tens of steps of a process run up to 30% slower
 than the rest, so every timed configuration is first warmed up for at least
@@ -69,6 +71,14 @@ GROUP_FOLD_VALU = {"int8": 5, "bf6": 3}
 MIN_WARM_STEPS = 200
 MIN_WARM_SECONDS = 0.2
 FLUSH_BYTES = 512 << 20
+
+
+def packed_gemm(lin, jq, cus):
+    """The tile height of the packed engine's GEMM for a linear, what its codes become, and that format's peak."""
+    rows = jq.jq_gemm_plan(lin.M, lin.N, lin.K, cus)
+    if rows >= 192:  # the kernel for many tiles and long K
+        return rows, "E2M3 (widened int4 codes) on the 6-bit MFMA, exact fp32 sums", PEAK_FP6_TOPS
+    return rows, "int8 (widened int4 codes), int32 accumulation", PEAK_INT8_TOPS
 
 
 def parse_args():
@@ -580,11 +590,11 @@ def operand_study(torch, jq, lin, prep, clock, launches=200):
 def full_rounds(torch, jq, workloads, launches=100):
     """Both engines' GEMMs on a shape whose output tiles fill whole rounds of
     the chip's block slots (8192 x 12288 -> 4096: 512 tiles of 256 x 256 for
-    the bf6 engine's 256 one-block CUs, 1024 tiles of 128 x 256 for the int8
-    engine's 512 two-block slots), next to the FLUX MLP-down shape
+    256 one-block CUs, on both engines), next to the FLUX MLP-down shape
     (9216 x 12288 -> 3072), whose tiles leave the last round part-empty.
     Inputs have the MLP-down statistics."""
     base = workloads.FLUX_MLP.linears[1]
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
     full = workloads.Linear("full_rounds_8192x12288x4096", M=8192, K=12288, N=4096, x_dist=base.x_dist,
                             x_seed=base.x_seed, outlier_frac=base.outlier_frac,
                             outlier_factor=base.outlier_factor, w_std=base.w_std, w_seed=base.w_seed)
@@ -607,7 +617,7 @@ def full_rounds(torch, jq, workloads, launches=100):
             torch.cuda.synchronize()
             us = e0.elapsed_time(e1) / launches * 1e3
             tops = lin.ops / us / 1e6
-            peak = PEAK_FP6_TOPS if eng == "bf6" else PEAK_INT8_TOPS
+            peak = PEAK_FP6_TOPS if eng == "bf6" else packed_gemm(lin, jq, cus)[2]
             out.append({"linear": lin.name, "M": lin.M, "K": lin.K, "N": lin.N, "engine": eng, "avg_us": us,
                         "TOPS": tops, "frac_mfma_peak": tops / peak, "pct_int8_peak": 100 * tops / PEAK_INT8_TOPS})
             log(f"full rounds {lin.name} {eng}: {us:.1f} us, {tops:.0f} TOPS ({100 * tops / peak:.1f}% of its peak)")
@@ -783,6 +793,7 @@ def main():
     copy = time_copy(torch)
     log(f"device copy: {copy['GBs_read_plus_write']:.0f} GB/s read + write")
 
+    props = torch.cuda.get_device_properties(0)
     # Per-kernel durations: the two kernels each linear launches, bracketed by
     # events on the stream they run on, for both engines.
     n_launch = max(args.steps, 20)
@@ -794,7 +805,7 @@ def main():
             code_bytes = jq.jq_f6_operand_bytes(lin.M, lin.K) if engine == "bf6" else lin.M * lin.K // 2
             q_bytes = 2 * lin.M * lin.K + code_bytes + 4 * lin.M
             g_ops = 2 * lin.M * lin.N * lin.K
-            peak = PEAK_FP6_TOPS if engine == "bf6" else PEAK_INT8_TOPS
+            peak = PEAK_FP6_TOPS if engine == "bf6" else packed_gemm(lin, jq, props.multi_processor_count)[2]
             q_gbs = q_bytes / tq_us / 1e3
             kernels.append({"engine": engine, "linear": lin.name, "kernel": "quantize_rows", "avg_us": tq_us,
                             "algorithmic_bytes": q_bytes, "achieved_GBs": q_gbs,
@@ -851,7 +862,6 @@ def main():
                         args.secondary_filter)
     clock.stop()
 
-    props = torch.cuda.get_device_properties(0)
     out = {
         "metric": "W4A4 linear effective TOPS + % int8 MFMA peak at FLUX-12B MLP shape",
         "value": value,
@@ -892,9 +902,9 @@ def main():
                      "pct_int8_peak": 100.0 * wl.ops / (us_int8 * 1e-6) / 1e12 / PEAK_INT8_TOPS,
                      "per_step_us": r8["per_step_us"], "warmup_steps": r8["warmup_steps"],
                      "clock": r8.get("clock"),
-                     "gemm_plan": {l.name: {"tile_rows": jq.jq_gemm_plan(l.M, l.N, l.K, props.multi_processor_count)}
-                                   for l in wl.linears},
-                     "dtype": "int8 (widened int4 codes), int32 accumulation"},
+                     "gemm_plan": {l.name: dict(zip(("tile_rows", "dtype", "peak_TOPS"),
+                                                    packed_gemm(l, jq, props.multi_processor_count)))
+                                   for l in wl.linears}},
             "outputs_bit_identical": bool(engines_equal),
         },
         "device_copy": copy,

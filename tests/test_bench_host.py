@@ -12,7 +12,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 
 import bench  # noqa: E402
-from paper_2609_33601_amd import workloads  # noqa: E402
+from paper_2609_33601_amd import jq, workloads  # noqa: E402
 
 
 def test_more_than_one_gpu_is_refused():
@@ -27,6 +27,19 @@ def test_headline_workload_is_the_flux_mlp_pair():
     assert (up.M, up.K, up.N) == (4608, 3072, 12288) and up.bias_std is not None
     assert (down.M, down.K, down.N) == (9216, 12288, 3072) and down.bias_std is None
     assert workloads.FLUX_MLP.ops == 2 * (4608 * 3072 * 12288 + 9216 * 12288 * 3072)
+
+
+@pytest.mark.skipif(not os.path.exists(jq.LIB_PATH), reason="libjq.so not built (run __graft_entry__.build())")
+def test_packed_engine_is_labelled_by_the_kernel_that_runs():
+    from tests.routes import route
+
+    for wl in workloads.WORKLOADS.values():
+        for l in wl.linears:
+            r = route("w4a4", l.M, l.K, l.N)
+            rows, dtype, peak = bench.packed_gemm(l, jq, 256)
+            assert rows == r.rows
+            assert (peak == bench.PEAK_FP6_TOPS) == dtype.startswith("E2M3") == (r.kernel == "wide"), l.name
+    assert all(bench.packed_gemm(l, jq, 256)[2] == bench.PEAK_FP6_TOPS for l in workloads.FLUX_MLP.linears)
 
 
 @pytest.mark.parametrize("linear", ["mlp_down", "mlp_up"])
