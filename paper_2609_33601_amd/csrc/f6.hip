@@ -64,14 +64,16 @@
 // memory path at 64 bytes per clock, 768 clocks.  With eight waves per block,
 // four bands each, the two waves of a SIMD loaded the same weights twice (72
 // KiB, 1152 clocks) and every wave had half the MFMAs to hide its other
-// instructions under; the stage took 0.72 us and takes 0.59 us now:
-// 4096 x 12288 -> 4096 74 -> 66 us, 9216 x 12288 -> 3072 139 -> 119 us.  One
-// wave gives an XCD four tile heights, since no second wave has to have the
-// same work: 6000 x 12288 -> 4096 in 192-row tiles 158 -> 137 us, 4608 x 8192
-// -> 1024 in 160-row tiles 50 -> 36 us.
-// The rest is the stages' own stalls and the epilogue: about 4 us a tile at
-// NFM = 8, its vector arithmetic (two multiplies and half a conversion per
-// output, 256 outputs a lane) with only one wave per SIMD to run it.
+// instructions under: 4096 x 12288 -> 4096 85 -> 76 us, 9216 x 12288 -> 3072
+// 153 -> 131 us (codes of a heavy-tailed activation, back to back; both sides of
+// every pair here in one run).  One wave per SIMD allows four tile heights, since
+// no second wave has to have the same work: in 192-row tiles 6000 x 12288 ->
+// 4096 152 -> 119 us and 3000 x 4096 -> 4096 34 -> 25 us.
+// The rest is the stages' own stalls and what a tile costs beside its stages,
+// 8.6 us at NFM = 8 by the fit of f6_tile_bands (the first loads, the epilogue
+// and its stores); about 4 us of it are the epilogue's vector arithmetic (two
+// multiplies and half a conversion per output, 256 outputs a lane) with only one
+// wave per SIMD to run it.
 //   * Activations: shared by the four waves, staged through LDS.  A stage is
 //     3 KiB per band, consecutive in memory, moved by buffer_load ... lds (no
 //     registers) into a ring of three stage slots, three stages ahead.
@@ -1523,7 +1525,7 @@ int64_t f6_operand_bytes(int64_t rows, int64_t K) { return (rows + 31) / 32 * f6
 // The GEMM's tile height in bands of 32 rows, 5 .. 8 (one block per CU) or 4
 // (two), and the estimate in ns it was picked by, for the XCD with most tiles:
 //   one block per CU: its rounds, each 38 b + 280 ns per 128 codes and 1080 b
-//   for the epilogue (b bands);
+//   for all that a tile costs beside its stages (b bands);
 //   two blocks per CU: 720 ns per 128 codes and 5600 for each round of two
 //   tiles per CU, 378 and 4300 for a last round with one tile per CU or fewer.
 // Fitted to 187 shapes (M 768..9216, K 128..15360, N 1024..12288) on codes of
