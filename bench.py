@@ -37,6 +37,10 @@ passed, its outputs compared with the GPU's), single-threaded on the tiny and
 the attention-projection workloads, and as a Python-integer brute force on the
 tiny one.
 
+The line stays short enough for a reader who keeps the last few kilobytes of a
+run's output; the parts it leaves out (per-launch spreads, the linears of the
+secondary layers) go to stderr, as one JSON line behind `[bench] detail`.
+
 `secondary` reports, from the same run, the same measurement for other
 layers: the FLUX MLP step with ternary weights (W1.58A4, on both engines) and
 group-wise (group64, on both engines, with the bound its fp32 group fold puts
@@ -729,7 +733,7 @@ def secondary(torch, jq, workloads, steps, warmup, n_launch, only=""):
         tops = wl.ops / (us * 1e-6) / 1e12
         layer = layer_names[fmt]
         per = per_linear_times(torch, preps, n_launch)
-        rec = {"workload": wl.description, "layer": layer, "us_per_step": us, "effective_TOPS": tops,
+        rec = {"name": wl.name, "workload": wl.description, "layer": layer, "us_per_step": us, "effective_TOPS": tops,
                "pct_int8_peak": 100.0 * tops / PEAK_INT8_TOPS, "warmup_steps": r["warmup_steps"],
                "per_step_us": r["per_step_us"],
                "linears": [{"name": p.lin.name, "M": p.lin.M, "K": p.lin.K, "N": p.lin.N,
@@ -749,6 +753,28 @@ def secondary(torch, jq, workloads, steps, warmup, n_launch, only=""):
         del preps
         torch.cuda.empty_cache()
     return out
+
+
+def rounded(x):
+    """The same values with floats to six significant digits."""
+    if isinstance(x, float):
+        return float(f"{x:.6g}")
+    if isinstance(x, dict):
+        return {k: rounded(v) for k, v in x.items()}
+    return [rounded(v) for v in x] if isinstance(x, (list, tuple)) else x
+
+
+def short_line(out):
+    """The line that is printed: `out` without the parts that only the detail on stderr has."""
+    exact = ("value", "ms_per_step")
+    line = {k: v if k in exact else rounded(v) for k, v in out.items()}
+    line["kernels"] = [{k: v for k, v in rec.items() if k != "per_launch_us"} for rec in line["kernels"]]
+    if line["secondary"] is not None:
+        line["secondary"] = [{"name": r["name"], "layer": r["layer"], "us_per_step": r["us_per_step"],
+                              "median_us": r["per_step_us"]["median"], "effective_TOPS": r["effective_TOPS"]}
+                             | ({"fold_bound_frac": r["valu_fold_bound"]["frac"]} if "valu_fold_bound" in r else {})
+                             for r in line["secondary"]]
+    return line
 
 
 def main():
@@ -919,7 +945,8 @@ def main():
         out["overlap_study"] = ovl
     if fr is not None:
         out["full_rounds"] = fr
-    print(json.dumps(out), flush=True)
+    log("detail " + json.dumps({"kernels": out["kernels"], "secondary": sec}))
+    print(json.dumps(short_line(out)), flush=True)
 
 
 if __name__ == "__main__":

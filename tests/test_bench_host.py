@@ -82,3 +82,20 @@ def test_group_fold_bound_uses_the_valu_peak():
     # 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz of non-packed fp32 VALU
     assert bench.PEAK_VALU_LANE_OPS == 256 * 4 * 16 * 2.4e9
     assert bench.GROUP_FOLD_VALU == {"int8": 5, "bf6": 3}
+
+
+def test_line_keeps_its_values_and_stays_short():
+    spread = {k: 270.62550187110901 for k in ("median", "p10", "p90", "min", "max")}
+    rec = {"name": "dllm_block", "workload": "w" * 120, "layer": "W4A4 group128 (int8 engine)", "us_per_step": 1214.2512345,
+           "effective_TOPS": 1131.88441, "pct_int8_peak": 22.6, "per_step_us": spread, "linears": [{"name": "x"}] * 4,
+           "valu_fold_bound": {"frac": 0.5622126176289962}}
+    out = {"metric": "m", "value": 3836.009971791953, "ms_per_step": 0.2720736026763916, "per_step_us": spread,
+           "steps": 20, "vs_baseline": None, "kernels": [{"engine": "bf6", "avg_us": 1 / 3, "per_launch_us": spread}] * 8,
+           "secondary": [rec] * 16}
+    line = bench.short_line(out)
+    assert line["value"] == out["value"] and line["ms_per_step"] == out["ms_per_step"] and line["steps"] == 20
+    assert line["per_step_us"]["median"] == 270.626 and line["kernels"][0] == {"engine": "bf6", "avg_us": 0.333333}
+    assert line["secondary"][0] == {"name": "dllm_block", "layer": rec["layer"], "us_per_step": 1214.25,
+                                    "median_us": 270.626, "effective_TOPS": 1131.88, "fold_bound_frac": 0.562213}
+    assert len(json.dumps(line["secondary"])) < 3500
+    assert bench.short_line({**out, "secondary": None})["secondary"] is None
