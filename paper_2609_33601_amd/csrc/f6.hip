@@ -1141,8 +1141,8 @@ __global__ __launch_bounds__(64 * kF6Waves, PER_CU) void w4a4_f6_gemm_kernel(
 // (4608 x 3072 -> 12288 and back).  The walk over the groups is therefore
 // software-pipelined: read, multiply and fold in turn left a wave waiting
 // about five times per stage for LDS and the MFMAs, and addresses and the
-// joining of operand parts took a tenth of the vector instructions (309 and
-// 297 us; 274 and 272 us now; at G = 128 210 and 205 -> 195 and 196 us).
+// joining of operand parts took a tenth of the vector instructions (306 and
+// 303 us; 274 and 267 us now; at G = 128 198 and 207 -> 187 and 197 us).
 //
 // Block tile 128 (m) x 128 (n), four waves, two blocks per CU; wave (wm, wn)
 // owns activation bands 2wm, 2wm + 1 and weight bands 2wn, 2wn + 1 of the
