@@ -1156,7 +1156,9 @@ __global__ __launch_bounds__(64 * kF6Waves, PER_CU) void w4a4_f6_gemm_kernel(
 // with no memory fence, after which the slot of the stage before takes the
 // loads of the stage three ahead of that one.  Operand bands, rows or columns
 // past M or N read as zero (outside the buffers).
-template <int G, Epilogue EPI, bool HAS_BIAS>
+//
+// ONE: K is a single group of 64 codes.
+template <int G, Epilogue EPI, bool HAS_BIAS, bool ONE>
 __global__ __launch_bounds__(256, 2) void w4a4g_f6_gemm_kernel(
     const uint8_t* __restrict__ xf6, const float* __restrict__ sx, int M, int mbands,
     const uint8_t* __restrict__ wf6, const float* __restrict__ sw, int N, int nbands, int ksteps, int KG,
@@ -1384,7 +1386,7 @@ __global__ __launch_bounds__(256, 2) void w4a4g_f6_gemm_kernel(
   __builtin_amdgcn_sched_barrier(0);
   using Set0 = std::integral_constant<int, 0>;
   using Set1 = std::integral_constant<int, 1>;
-  if constexpr (G == 64) {
+  if constexpr (G == 64 && !ONE) {
     int k = 0;
     for (int u = 0; u < T; ++u) {
       const int kn = k == 2 ? 0 : k + 1;
@@ -1394,15 +1396,17 @@ __global__ __launch_bounds__(256, 2) void w4a4g_f6_gemm_kernel(
       k = kn;
     }
   } else {
-    int k = 0;
-    for (int u = 0; u + 1 < T; ++u) {
-      k = k == 2 ? 0 : k + 1;
-      group(Set0{}, true, u, k, 0);
+    if constexpr (!ONE) {
+      int k = 0;
+      for (int u = 0; u + 1 < T; ++u) {
+        k = k == 2 ? 0 : k + 1;
+        group(Set0{}, true, u, k, 0);
+      }
     }
     // The last group, with nothing to run ahead to: 4096 x 256 -> 4096 12.1 ->
-    // 11.2 us, 1948 x 128 -> 8768 13.3 -> 11.9.  (G = 64, where a group is half
-    // as long: the loop's two groups and a last one apart do not fit the
-    // registers.)
+    // 11.2 us, 1948 x 128 -> 8768 13.3 -> 11.9.  (With G = 64 the loop's two
+    // groups and a last one apart do not fit the registers, so only a single
+    // group has its own kernel: 7460 x 64 -> 4608 17.2 -> 15.5 us.)
     products(a1, 1);
     fold(a0[0], 0, 0, 0);
     fold(a0[1], 0, 1, 0);
@@ -1668,18 +1672,21 @@ hipError_t launch_w4a4g_f6_gemm(Epilogue epi, const uint8_t* xf6, const float* s
   const int mbands = static_cast<int>((M + 31) / 32), nbands = static_cast<int>((N + 31) / 32);
   const int KG = static_cast<int>(K / G);
   const int Mi = static_cast<int>(M), Ni = static_cast<int>(N);
-#define JQ_F6G(GG, E, B)                                                                                       \
-  hipLaunchKernelGGL((w4a4g_f6_gemm_kernel<GG, E, B>), dim3(blocks), dim3(256), 0, st, xf6, sx, Mi, mbands, wf6, \
+#define JQ_F6G(GG, E, B, O)                                                                                       \
+  hipLaunchKernelGGL((w4a4g_f6_gemm_kernel<GG, E, B, O>), dim3(blocks), dim3(256), 0, st, xf6, sx, Mi, mbands, wf6, \
                      sw, Ni, nbands, ksteps, KG, bias, out, tiles_m, tiles_n)
-  if (G == 64) {
-    if (epi == Epilogue::kF32) JQ_F6G(64, Epilogue::kF32, false);
-    else if (bias != nullptr) JQ_F6G(64, Epilogue::kBf16, true);
-    else JQ_F6G(64, Epilogue::kBf16, false);
+#define JQ_F6G_EPI(GG, O)                                             \
+  if (epi == Epilogue::kF32) JQ_F6G(GG, Epilogue::kF32, false, O);    \
+  else if (bias != nullptr) JQ_F6G(GG, Epilogue::kBf16, true, O);     \
+  else JQ_F6G(GG, Epilogue::kBf16, false, O);
+  if (G == 128) {
+    JQ_F6G_EPI(128, false)
+  } else if (KG == 1) {
+    JQ_F6G_EPI(64, true)
   } else {
-    if (epi == Epilogue::kF32) JQ_F6G(128, Epilogue::kF32, false);
-    else if (bias != nullptr) JQ_F6G(128, Epilogue::kBf16, true);
-    else JQ_F6G(128, Epilogue::kBf16, false);
+    JQ_F6G_EPI(64, false)
   }
+#undef JQ_F6G_EPI
 #undef JQ_F6G
   return hipGetLastError();
 }
